@@ -44,7 +44,7 @@ __host__ __device__ inline AdjLds adj_lds_layout(int ns, int n_layers, int n_pix
   const int nl = 2 * ns - 1, np2 = n_pix * n_pix;
   AdjLds a;
   const int ub = nl * adj_u_pitch(ns) * 8, gbb = (np2 * 4 + 7) & ~7, gzb = np2 * 8;
-  const int e_end = (ns * otf_pitch(ns) * 8 + 15) & ~15;
+  const int e_end = (ns * ns * 8 + 15) & ~15;
   if (gather && e_end + ub + gbb + 2 * gzb <= f.stab_off) {
     a.u_off = e_end;
     a.gb_off = a.u_off + ub;
@@ -182,7 +182,7 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
   float* gl = ap.grad_layers + (int64_t)b * p.layer_stride;
   for (int q = lane; q < NS * NS; q += kWave) {
     const int r = q / NS, c = q - r * NS;
-    const float2 e = E[r * Otf<NS>::kEP + c];
+    const float2 e = E[q];
     if (e.x == 0.0f && e.y == 0.0f) continue;  // dark pixel
     float2 V = make_float2(0.0f, 0.0f);
 #pragma unroll 2
@@ -191,7 +191,7 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
 #pragma unroll
       for (int c2 = 0; c2 < NS; ++c2) {
         const float2 u = urow[c2];
-        const float2 f = E[r2 * Otf<NS>::kEP + c2];
+        const float2 f = E[r2 * NS + c2];
         // u * conj(f)
         V.x = fmaf(u.x, f.x, fmaf(u.y, f.y, V.x));
         V.y = fmaf(u.y, f.x, fmaf(-u.x, f.y, V.y));

@@ -6,6 +6,8 @@
 // FFT path (wfs_fft.h) from zero-padded transforms.  Both end in the same noise + centre of
 // gravity stage.
 
+#include <cmath>
+
 #include "wfs_fft.h"
 #include "wfs_otf.h"
 #include "wfs_project.h"
@@ -105,11 +107,23 @@ hipError_t launch_forward(const FwdParams& p, int ns, hipStream_t st, const Side
   return launch_forward_ns(c, ns, st);
 }
 
-int foot_pitch(int ns) { return otf_pitch(ns + 2); }
+int foot_pitch(int ns) { return (ns + 2) | 1; }
 
-int otf_lds_bytes(int ns, int n_layers, int n_pix, bool with_taps, int foot_floats,
-                  int lag_parts) {
-  return otf_lds_layout(ns, n_layers, n_pix, with_taps, foot_floats, lag_parts).total;
+int otf_lds_bytes(int ns, int n_layers, int n_pix, bool with_taps, int foot_floats) {
+  return otf_lds_layout(ns, n_layers, n_pix, with_taps, foot_floats).total;
+}
+
+int otf_twiddle_count(int ns) { return otf_twiddles(ns); }
+
+// Twiddles of otf_corr for subaperture size ns (see kOtfTw).
+void otf_fill_twiddles(int ns, float2* out) {
+  const int Q = otf_q(ns);
+  for (int k0 = 0; k0 < Q; ++k0)
+    for (int i = 0; i < kOtfTw; ++i) {
+      const double a = i < 5 ? 2.0 * M_PI * (((i + 1) * k0) % Q) / Q
+                             : 2.0 * M_PI * ((i - 4) * k0) / (4.0 * Q);
+      out[k0 * kOtfTw + i] = make_float2((float)std::cos(a), (float)-std::sin(a));
+    }
 }
 
 int project_lds_bytes(int n_layers, int rows) {

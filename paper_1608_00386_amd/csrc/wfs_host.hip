@@ -51,8 +51,9 @@ hipError_t calib_poke(float* layers, const float* base, int64_t stride, int32_t 
                       int32_t n_chunk, float amp, hipStream_t st);
 hipError_t calib_diff(const float* slopes, int32_t h, int32_t n_slopes, int32_t n_chunk,
                       float amp, float* im, int64_t ld_im, hipStream_t st);
-int otf_lds_bytes(int ns, int n_layers, int n_pix, bool with_taps, int foot_floats,
-                  int lag_parts = kOtfLagParts);
+int otf_lds_bytes(int ns, int n_layers, int n_pix, bool with_taps, int foot_floats);
+int otf_twiddle_count(int ns);
+void otf_fill_twiddles(int ns, float2* out);
 int foot_pitch(int ns);
 int fft_wave_lds_bytes(int n_fft, int n_pix);
 bool fft_supported(int n_sub, int n_fft, int bin);
@@ -117,7 +118,7 @@ struct OtfGroup {
   int64_t n_tasks = 0;
   // LDS bytes per wave of this group's lag-domain waves in a launch without FFT-path blocks
   int lds_split = 0, lds_fused = 0, lds_foot = 0, lds_adj = 0;
-  int lds_split_lp[2] = {0, 0};  // split field with the lag row in 2 / 3 passes
+  const float2* otf_tw = nullptr;  // twiddles of the autocorrelation (device)
 };
 
 struct wfs_plan_s {
@@ -159,9 +160,7 @@ struct wfs_plan_s {
   bool adj_clear_grad = true;  // the layer grids leave gaps inside the stride
   int lds_split = 0, lds_fused = 0;  // LDS bytes per lag-domain wave, per schedule
   int lds_split_otf = 0, lds_fused_otf = 0;  // same, in a launch without FFT-path blocks
-  // the split field's figures with the lag row in 2 / 3 passes, and the current pass count
-  int lds_split_lp[2] = {0, 0}, lds_split_otf_lp[2] = {0, 0};
-  int lag_parts = kOtfLagParts;
+  int lag_passes = 2;        // wfs_plan_set_schedule's value, reported back
   int proj_lds = 0;          // bytes of LDS per projection block (all sensors)
   int proj_lds_fft = 0;      // same, FFT-path sensors only
   ProjTable proj_all{}, proj_fft{};  // the projection blocks of the current tile height
@@ -217,17 +216,6 @@ static void destroy_ovl(wfs_plan_s* P) {
 
 // Makes projection tile height i of the plan the current one (host only: the descriptors of
 // every height are on the device already, and each height gives the same bits).
-static void use_lag_parts(wfs_plan_s* P, int lp) {
-  const int i = lp == 3 ? 1 : 0;
-  P->lag_parts = lp;
-  P->lds_split = P->lds_split_lp[i];
-  P->lds_split_otf = P->lds_split_otf_lp[i];
-  for (OtfGroup& G : P->groups) G.lds_split = G.lds_split_lp[i];
-  P->base.lag_parts = lp;
-  P->base.lds_per_wave = P->lds_split;
-  P->base.lds_per_wave_otf = P->lds_split_otf;
-}
-
 static void use_proj_set(wfs_plan_s* P, int i) {
   const ProjSet& q = P->proj_sets[i];
   P->proj_set = i;
@@ -779,6 +767,12 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
   const size_t o_stab = push_table(blob, stab);
   const size_t o_wtab = push_table(blob, wtab);
   const size_t o_mtab = push_table(blob, mtab);
+  std::vector<size_t> o_otf_tw;
+  for (const OtfGroup& G : P->groups) {
+    std::vector<float2> tw((size_t)otf_twiddle_count(G.ns));
+    otf_fill_twiddles(G.ns, tw.data());
+    o_otf_tw.push_back(push_table(blob, tw));
+  }
   const size_t o_subidx = push_table(blob, subidx);
   const size_t o_foot = push_table(blob, foot);
   if (foot_cols.empty()) foot_cols.push_back(FootCol{});
@@ -898,11 +892,15 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     OtfGroup& G = P->groups[gi];
     fill_tasks(G.tasks, G.ids, P->n_valid);
     G.tasks.order = reinterpret_cast<const int2*>(P->d_blob + o_order) + order_off[gi];
+    G.otf_tw = reinterpret_cast<const float2*>(P->d_blob + o_otf_tw[gi]);
     G.n_tasks = (int64_t)G.tasks.per_real * batch;
     P->otf_tasks += G.n_tasks;
   }
   if (P->groups.empty()) fill_tasks(b.otf, otf_ids, P->n_valid);
-  else b.otf = P->groups[0].tasks;
+  else {
+    b.otf = P->groups[0].tasks;
+    b.otf_tw = P->groups[0].otf_tw;
+  }
   {  // FFT path: one task (wave) per spectrum chunk, Q^2 per subaperture
     std::vector<int32_t> units(P->n_valid);
     for (int s : fft_ids) {
@@ -942,8 +940,8 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
   for (int s : fft_ids)
     lds_fft = std::max(lds_fft, fft_wave_lds_bytes(sensors[s].n_fft,
                                                    sensors[s].n_fft / sensors[s].bin));
-  auto wave_lds = [&](bool taps, bool with_fft, int lag_parts = kOtfLagParts) {
-    int w = otf_ns ? otf_lds_bytes(otf_ns, n_layers, P->otf_max_npix, taps, 0, lag_parts) : 0;
+  auto wave_lds = [&](bool taps, bool with_fft) {
+    int w = otf_ns ? otf_lds_bytes(otf_ns, n_layers, P->otf_max_npix, taps, 0) : 0;
     if (with_fft) w = std::max(w, lds_fft);
     return std::max(16, (w + 15) & ~15);
   };
@@ -955,17 +953,14 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
                 lds_wave * kWavesPerBlock);
   }
   P->lds_fused = lds_wave;
-  for (int i = 0; i < 2; ++i) {
-    P->lds_split_lp[i] = wave_lds(false, true, 2 + i);
-    P->lds_split_otf_lp[i] = wave_lds(false, false, 2 + i);
-  }
+  P->lds_split = wave_lds(false, true);
+  P->lds_split_otf = wave_lds(false, false);
   // every group's LDS per wave, in launches without FFT-path blocks (group 0's launch with
   // them takes the larger figures above)
   bool adj_ok = true;
   for (OtfGroup& G : P->groups) {
     auto r16 = [](int x) { return std::max(16, (x + 15) & ~15); };
-    for (int i = 0; i < 2; ++i)
-      G.lds_split_lp[i] = r16(otf_lds_bytes(G.ns, n_layers, G.max_npix, false, 0, 2 + i));
+    G.lds_split = r16(otf_lds_bytes(G.ns, n_layers, G.max_npix, false, 0));
     G.lds_fused = r16(otf_lds_bytes(G.ns, n_layers, G.max_npix, true, 0));
     G.lds_foot = r16(otf_lds_bytes(G.ns, n_layers, G.max_npix, false, G.foot_floats));
     // the adjoint's form (gather unless asked for atomics), as wfs_adjoint decides it
@@ -1000,20 +995,8 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     b.foot_ent_per_frame = (int32_t)foot_ent;
   }
   P->lds_fused_otf = wave_lds(true, false);
-  {
-    // the lag row in 3 passes where that lets more blocks share a CU and the split launch
-    // runs more than two rounds of blocks (one 80 x 80 LGS: 1,158 blocks, 2 passes; eight
-    // realisations of six: 55,584 blocks, 3 passes); wfs_plan_tune times both
-    auto per_cu = [](int lds_wave) { return std::min(8, 163840 / (lds_wave * kWavesPerBlock)); };
-    int64_t blocks = 0;
-    for (const OtfGroup& G : P->groups) blocks += (G.n_tasks + kWavesPerBlock - 1) / kWavesPerBlock;
-    int lp = kOtfLagParts;
-    if (!P->groups.empty() &&
-        per_cu(P->groups[0].lds_split_lp[1]) > per_cu(P->groups[0].lds_split_lp[0]) &&
-        blocks > 2LL * 256 * per_cu(P->groups[0].lds_split_lp[0]))
-      lp = 3;
-    use_lag_parts(P, lp);
-  }
+  b.lds_per_wave = P->lds_split;
+  b.lds_per_wave_otf = P->lds_split_otf;
   P->adj_lds_per_wave = otf_ns ? P->groups[0].lds_adj : 16;
   if (!adj_ok) P->adj_lds_per_wave = 0;  // adjoint unsupported
   // FFT blocks first, padded to a multiple of 8 so the lag-domain blocks keep their XCD order
@@ -1247,6 +1230,7 @@ static hipError_t launch_groups(wfs_plan_t P, const FwdParams& p, hipStream_t st
     const OtfGroup& G = P->groups[g];
     FwdParams q = p;
     q.otf = G.tasks;
+    q.otf_tw = G.otf_tw;
     q.otf_blocks = (int32_t)((G.n_tasks + kWavesPerBlock - 1) / kWavesPerBlock);
     q.fft_blocks = 0;
     q.proj_blocks = 0;
@@ -1462,7 +1446,7 @@ int wfs_plan_schedule(wfs_plan_t P, int32_t* field, int32_t* frames, int32_t* xc
   if (xcd_remap) *xcd_remap = P->base.xcd_remap;
   if (fft_launch) *fft_launch = P->base.fft_inline;
   if (proj_rows) *proj_rows = P->proj_sets[P->proj_set].rows;
-  if (lag_passes) *lag_passes = P->lag_parts;
+  if (lag_passes) *lag_passes = P->lag_passes;
   return WFS_OK;
 }
 
@@ -1510,7 +1494,7 @@ int wfs_plan_set_schedule(wfs_plan_t P, int32_t field, int32_t frames, int32_t x
   if (xcd_remap >= 0) P->base.xcd_remap = xcd_remap;
   if (fft_launch >= 0) P->base.fft_inline = fft_launch;
   use_proj_set(P, ps);
-  if (lag_passes > 0) use_lag_parts(P, lag_passes);
+  if (lag_passes > 0) P->lag_passes = lag_passes;
   return WFS_OK;
 }
 
@@ -1695,6 +1679,7 @@ int wfs_adjoint(wfs_plan_t P, const float* layers, const float* grad_slopes,
   for (size_t g = 1; g < P->groups.size() && e == hipSuccess; ++g) {
     AdjParams ag = a;  // the other subaperture sizes add their sensors' shares
     ag.f.otf = P->groups[g].tasks;
+    ag.f.otf_tw = P->groups[g].otf_tw;
     ag.f.lds_per_wave = P->groups[g].lds_adj;
     e = launch_adjoint(ag, P->groups[g].ns, false, false, (hipStream_t)stream);
   }
@@ -1744,14 +1729,14 @@ int wfs_plan_tune(wfs_plan_t P, const float* layers, int32_t iters, double* best
   };
   const FwdParams keep = P->base;
   const int keep_split = P->split, keep_foot = P->foot, keep_frames = P->frames;
-  const int keep_ps = P->proj_set, keep_lp = P->lag_parts;
+  const int keep_ps = P->proj_set;
   // candidates (field, frames, block order, FFT-path blocks in the lag-domain launch,
   // projection tile height), timed on nf frames in a row (the stepping loop the plan serves);
   // only schedules whose single frames and frames in a row give the same bits: the gather
   // field steps frame by frame, the split and footprint fields share their bits with
   // pipelined and one-launch frames; every tile height gives the same bits
   struct Cand {
-    int field, frames, remap, inl, ps, lp;
+    int field, frames, remap, inl, ps;
   };
   std::vector<Cand> cands;
   const bool has_fft = P->fft_tasks > 0, mixed = P->fft_tasks > 0 && P->otf_tasks > 0;
@@ -1761,37 +1746,32 @@ int wfs_plan_tune(wfs_plan_t P, const float* layers, int32_t iters, double* best
   const int n_ps = (int)P->proj_sets.size();
   // the tile heights of the projection kernel, for a schedule that launches it (the split
   // field, and the FFT-path sensors of any field)
-  // and, for the split field's spot kernel, the lag row in 2 or 3 passes
   auto add = [&](Cand c) {
     const bool proj = c.field == 1 || has_fft;
-    const bool split_spots = c.field == 1 || c.frames == 1 || c.frames == 3;
-    for (int ps = 0; ps < (proj ? n_ps : 1); ++ps)
-      for (int lp = 2; lp <= (split_spots ? 3 : 2); ++lp) {
-        c.ps = proj ? ps : keep_ps;
-        c.lp = split_spots ? lp : keep_lp;
-        cands.push_back(c);
-      }
+    for (int ps = 0; ps < (proj ? n_ps : 1); ++ps) {
+      c.ps = proj ? ps : keep_ps;
+      cands.push_back(c);
+    }
   };
   for (int remap = 0; remap < 2; ++remap)
     for (int inl = 0; inl < (mixed ? 2 : 1); ++inl) {
-      if (!(fl & (WFS_FLAG_SPLIT | WFS_FLAG_FOOTPRINT))) add({0, 0, remap, inl, 0, 0});
+      if (!(fl & (WFS_FLAG_SPLIT | WFS_FLAG_FOOTPRINT))) add({0, 0, remap, inl, 0});
       if (phase_ok && !(fl & WFS_FLAG_FUSED)) {
         if (!((fl & WFS_FLAG_FOOTPRINT) && foot1)) {
-          add({1, 0, remap, inl, 0, 0});
-          add({1, 1, remap, inl, 0, 0});
-          if (P->ovl.stream) add({1, 3, remap, inl, 0, 0});
+          add({1, 0, remap, inl, 0});
+          add({1, 1, remap, inl, 0});
+          if (P->ovl.stream) add({1, 3, remap, inl, 0});
         }
       }
       if (inl == 0 && P->foot_ok && !(fl & (WFS_FLAG_FUSED | WFS_FLAG_SPLIT)) &&
           (foot1 || phase_ok))
-        add({foot1 ? 2 : 1, 2, remap, 0, 0, 0});
+        add({foot1 ? 2 : 1, 2, remap, 0, 0});
     }
   auto apply = [&](const Cand& c) {
     P->base = keep;
     P->base.xcd_remap = c.remap;
     P->base.fft_inline = c.inl;
     use_proj_set(P, c.ps);
-    use_lag_parts(P, c.lp);
     P->split = c.field == 1;
     P->foot = c.field == 2;
     P->frames = c.frames;
@@ -1856,7 +1836,6 @@ int wfs_plan_tune(wfs_plan_t P, const float* layers, int32_t iters, double* best
   if (e != hipSuccess) {
     P->base = keep;
     use_proj_set(P, keep_ps);
-    use_lag_parts(P, keep_lp);
     P->split = keep_split;
     P->foot = keep_foot;
     P->frames = keep_frames;

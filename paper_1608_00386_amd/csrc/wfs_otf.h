@@ -11,8 +11,8 @@
 // folding the lags modulo n_pix.  So the binned image is
 //     B[q] = c Re sum_{K} P[K] e^{2 pi i K.q / n_pix},
 //     P[K] = sum_{k = K mod n_pix, half plane} w_k A[k] Kel[k] s(kx) s(ky),
-// (w = 1 on the ky = 0 row, 2 above it, using A[-k] = conj A[k]) which needs n_sub^2 complex
-// multiply-adds per row pair instead of two N x N transforms, and no N x N array at all.
+// (w = 1 on the ky = 0 row, 2 above it, using A[-k] = conj A[k]): no N x N array at all.
+// The autocorrelation itself runs through a short DFT of each field row (otf_corr).
 // The result equals the FFT definition up to rounding; the FP64 oracle checks it.
 #pragma once
 
@@ -25,72 +25,72 @@ namespace wfs {
 // Lag-domain path
 // ------------------------------------------------------------------------------------------
 
-__host__ __device__ constexpr int otf_pitch(int n) { return n | 1; }
+// Sizes of the autocorrelation stage of one subaperture (otf_corr): DFTs of F = 4 Q >=
+// 2 n_sub - 1 points, so that no lag wraps around.
+__host__ __device__ constexpr int otf_q(int ns) { return (2 * ns + 2) / 4; }
+// Lane groups that share the row products of one frequency: groups of 16 or 32 lanes.
+__host__ __device__ constexpr int otf_groups(int ns) { return 4 * otf_q(ns) <= 16 ? 4 : 2; }
+// Rows of the row transforms: the field's, and zero rows for the groups' row offsets.
+__host__ __device__ constexpr int otf_rows(int ns) { return ns + otf_groups(ns) - 1; }
+// Row pitch (float2) of the row products: even (16-byte loads), and rows on different banks.
+__host__ __device__ constexpr int otf_c_pitch(int ns) { return 4 * otf_q(ns) + 2; }
 
-template <int NS, int LP = kOtfLagParts>
+template <int NS>
 struct Otf {
-  static constexpr int kJobs = NS * (NS + 1) / 2;  // row pairs (dy, r), dy >= 0
-  static constexpr int kLags = 2 * NS - 1;         // dx = -(NS-1) .. NS-1
-  static constexpr int kParts = LP;                // passes over the lag row
-  static constexpr int kChunk = (kLags + kParts - 1) / kParts;  // lag columns per pass
-  // odd LDS pitches (float2) of the field rows and of the partial lag rows: lanes reading
-  // different rows of E, or writing their own partial row, fall on distinct bank pairs
-  static constexpr int kEP = otf_pitch(NS);
-  static constexpr int kPS = otf_pitch(kChunk);
-  static constexpr int kRounds = (kJobs + kWave - 1) / kWave;
-  static constexpr int kJobsPerRound = (kJobs + kRounds - 1) / kRounds;
-  // one round (n_sub <= 10): partial-row slots grouped by pairs of lag rows (dy, NS - 1 - dy),
-  // NS + 1 slots a pair (the middle row of an odd NS pairs with itself and leaves slots free)
-  static constexpr int kPairs = (NS + 1) / 2;
-  static constexpr int kSlots = kRounds == 1 ? kPairs * (NS + 1) : kJobsPerRound;
+  static constexpr int kLags = 2 * NS - 1;       // dx = -(NS-1) .. NS-1
+  static constexpr int kQ = otf_q(NS);
+  static constexpr int kF = 4 * kQ;              // DFT points of one field row
+  static constexpr int kGroups = otf_groups(NS);
+  static constexpr int kRows = otf_rows(NS);
+  static constexpr int kCP = otf_c_pitch(NS);
+  static constexpr int kAP = kF;                 // row pitch (float2) of the lag array
 };
 
-// Partial-row slots of one round (the LDS layout's `part` region).
-__host__ __device__ constexpr int otf_part_rows(int ns) {
-  return (ns * (ns + 1) / 2 + kWave - 1) / kWave == 1
-             ? ((ns + 1) / 2) * (ns + 1)
-             : (ns * (ns + 1) / 2 + ((ns * (ns + 1) / 2 + kWave - 1) / kWave) - 1) /
-                   ((ns * (ns + 1) / 2 + kWave - 1) / kWave);
-}
+// Twiddles of otf_corr, one row of kOtfTw float2 per residue k0 < Q: exp(-2 pi i m k0 / Q),
+// m = 1 .. 5, then exp(-2 pi i s k0 / F), s = 1 .. 3.
+constexpr int kOtfTw = 8;
+__host__ __device__ constexpr int otf_twiddles(int ns) { return otf_q(ns) * kOtfTw; }
 
 // Per-wave LDS layout (bytes), shared with the host sizing code:
-//   E [n_sub][pitch] float2 (pitch = n_sub rounded up to odd) | AW [n_sub][2 n_sub - 1]
-//   float2 (weighted lag sums) |
+//   E [n_sub][n_sub] float2 |
 //   union( taps [n_layers][2 n_sub] Tap (fused gather and adjoint only),
-//          partial lag rows (one round, one pass over the lag row at a time:
-//          [jobs][ceil((2 n_sub - 1) / lag passes) rounded up to odd] float2),
-//          P (later B) + Z (after the last round) ) |
-//   tables: s(k) [2 n_sub - 1] float2, twiddles [n_pix] float2
+//          row transforms G [4][rows][Q] float2, then row products C [n_sub][pitch] float2
+//          over them, lags AW [n_sub][F] float2 behind C, then P (later B) + Z over C ) |
+//   tables: twiddles of otf_corr [Q][kOtfTw] float2, s(k) [2 n_sub - 1] float2, image
+//           twiddles [n_pix] float2
 // With a staged footprint (foot_floats > 0) the field stage also lays out, from offset 0
-// (E, AW, the union and the tables are free until the field is formed): stencil entries
+// (E, the union and the tables are free until the field is formed): stencil entries
 // [n_layers][2 n_sub] FootTap (12 bytes) | the footprint [foot_floats] float (first holding
 // the window origins, [n_layers][2] int).  The tables are then copied in after the window
 // has been read.
 struct OtfLds {
-  int e_off, stab_off, wtab_off, aw_off, taps_off, part_off, p_off, z_off, b_off;
+  int e_off, tw_off, stab_off, wtab_off, aw_off, taps_off, g_off, c_off, p_off, z_off, b_off;
   int fw_off, fp_off, total;
 };
 
 __host__ __device__ inline OtfLds otf_lds_layout(int ns, int n_layers, int n_pix,
-                                                 bool with_taps = true, int foot_floats = 0,
-                                                 int lag_parts = kOtfLagParts) {
+                                                 bool with_taps = true, int foot_floats = 0) {
   OtfLds o;
-  const int jobs = otf_part_rows(ns), lags = 2 * ns - 1, np2 = n_pix * n_pix;
+  const int lags = 2 * ns - 1, np2 = n_pix * n_pix;
   o.e_off = 0;
-  o.aw_off = ns * otf_pitch(ns) * 8;
-  const int u0 = (o.aw_off + ns * lags * 8 + 15) & ~15;
+  const int u0 = (ns * ns * 8 + 15) & ~15;
   const int taps = 2 * ns * n_layers * 16;
-  const int part = jobs * otf_pitch((lags + lag_parts - 1) / lag_parts) * 8;
+  const int g = 4 * otf_rows(ns) * otf_q(ns) * 8;
+  const int c = ns * otf_c_pitch(ns) * 8;
   o.taps_off = u0;
-  o.part_off = u0;
-  o.p_off = u0;  // the fold writes P after the last round has read its partial rows
+  o.g_off = u0;
+  o.c_off = u0;
+  o.p_off = u0;  // the fold reads the lags and writes P: they do not meet
   o.z_off = o.p_off + np2 * 8;
   o.b_off = o.p_off;  // B overwrites P: the image's second pass reads only Z
+  o.aw_off = u0 + (c > np2 * 8 ? c : np2 * 8);
   int end = o.z_off + np2 * 8;
   if (o.p_off + 1024 > end) end = o.p_off + 1024;  // matrix-core image: 16 x 16 floats
-  if (u0 + part > end) end = u0 + part;
+  if (u0 + g > end) end = u0 + g;
+  if (o.aw_off + ns * 4 * otf_q(ns) * 8 > end) end = o.aw_off + ns * 4 * otf_q(ns) * 8;
   if (with_taps && u0 + taps > end) end = u0 + taps;
-  o.stab_off = (end + 7) & ~7;
+  o.tw_off = (end + 15) & ~15;
+  o.stab_off = o.tw_off + otf_twiddles(ns) * 8;
   o.wtab_off = o.stab_off + lags * 8;
   end = o.wtab_off + n_pix * 8;
   o.fw_off = 0;
@@ -101,34 +101,10 @@ __host__ __device__ inline OtfLds otf_lds_layout(int ns, int n_layers, int n_pix
   return o;
 }
 
-template <int NS>
-__device__ __forceinline__ void job_of(int j, int& dy, int& r) {
-  int d = 0;
-  while (j >= NS - d) {
-    j -= NS - d;
-    ++d;
-  }
-  dy = d;
-  r = j;
-}
-
-template <int NS>
-__device__ __forceinline__ int job_base(int dy) {
-  return dy * NS - (dy * (dy - 1)) / 2;
-}
-
-// Row-pair job of partial-row slot j in the one-round layout (false: a free slot).
-template <int NS>
-__device__ __forceinline__ bool slot_job(int j, int& dy, int& r) {
-  const int q = j / (NS + 1), t = j - q * (NS + 1), nA = NS - q;
-  if (t < nA) {
-    dy = q;
-    r = t;
-    return true;
-  }
-  dy = NS - 1 - q;
-  r = t - nA;
-  return dy != q;
+// q / D for 0 <= q D < 2^16 (full-rate 24-bit multiply)
+template <int D>
+__device__ __forceinline__ int small_div(int q) {
+  return (int)(((uint32_t)q * (uint32_t)((65536 + D - 1) / D)) >> 16);
 }
 
 // Tap of a given layer for the lanes of one half-wave: the layer parameters are wave-uniform
@@ -191,6 +167,45 @@ __device__ __forceinline__ float field_ramp(const DevSensor& S, int r, int c) {
   return fmaf((float)c, S.ramp_x, (float)r * S.ramp_y);
 }
 
+// The wave's copies of the small tables (twiddles of otf_corr, lag phases s(k), image
+// twiddles: consecutive in the LDS layout) and the pupil amplitude of the lane's pixels.  They
+// are loaded at the start, so that their latency passes under the field's own loads, and
+// stored once the field stage leaves their LDS free.
+template <int NS>
+struct OtfTables {
+  static constexpr int kPPL = (NS * NS + kWave - 1) / kWave;  // pixels per lane
+  static constexpr int kFixed = otf_twiddles(NS) + 2 * NS - 1;
+  static constexpr int kPre = kFixed + 8 > kWave ? 2 : 1;     // entries per lane held early
+  float2 t[kPre];
+  uint8_t amp[kPPL];
+
+  __device__ __forceinline__ float2 entry(const FwdParams& p, const DevSensor& S, int k) const {
+    if (k < otf_twiddles(NS)) return p.otf_tw[k];
+    if (k < kFixed) return p.stab[S.stab_off + k - otf_twiddles(NS)];
+    return k < kFixed + S.n_pix ? p.wtab[S.wtab_off + k - kFixed] : make_float2(0.0f, 0.0f);
+  }
+  __device__ __forceinline__ void load(const FwdParams& p, const DevSensor& S,
+                                       const DevSubap& sb) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) t[i] = entry(p, S, lane + i * kWave);
+#pragma unroll
+    for (int i = 0; i < kPPL; ++i) {
+      const int q = min(lane + i * kWave, NS * NS - 1), r = small_div<NS>(q), c = q - r * NS;
+      amp[i] = p.mask[S.mask_off + (sb.a * NS + r) * S.n_pup + sb.b * NS + c];
+    }
+  }
+  __device__ __forceinline__ void store(const FwdParams& p, const DevSensor& S, char* wsm,
+                                        const OtfLds& lo) const {
+    float2* d = reinterpret_cast<float2*>(wsm + lo.tw_off);
+    const int lane = lane_id(), n = kFixed + S.n_pix;
+#pragma unroll
+    for (int i = 0; i < kPre; ++i)
+      if (lane + i * kWave < n) d[lane + i * kWave] = t[i];
+    for (int k = lane + kPre * kWave; k < n; k += kWave) d[k] = entry(p, S, k);
+  }
+};
+
 // Where the lag-domain field stage gets the phase (a compile-time choice, so that each kernel
 // only holds the registers of its own path).
 constexpr int kFieldGather = 0;  // bilinear stencils straight from the layers, per pixel
@@ -243,12 +258,11 @@ struct FootTap {
 // for bit.
 template <int NS>
 __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& S,
-                                           const DevSubap& sb, int sid, int b, int frame,
-                                           char* wsm, const OtfLds& lo, float* ph) {
+                                           const DevSubap& sb, int b, int frame, char* wsm, const OtfLds& lo, float* ph) {
   constexpr int NPIX = NS * NS;
   constexpr int PPL = (NPIX + kWave - 1) / kWave;
   constexpr int ROWS = NS + 2;                   // window rows loaded per column
-  constexpr int SLOT = otf_pitch(ROWS);          // LDS floats per window column
+  constexpr int SLOT = ROWS | 1;                 // LDS floats per window column (odd)
   constexpr int TPL = 2 * NS;       // stencil entries per layer: columns, then rows
   constexpr int LPP = kWave / TPL;  // layers per pass
   const int lane = lane_id();
@@ -256,7 +270,6 @@ __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& 
   FootTap* tab = reinterpret_cast<FootTap*>(wsm + lo.fw_off);  // [nl][2 NS]
   int* forg = reinterpret_cast<int*>(wsm + lo.fp_off);         // [nl][2], until step 2
   float* fp = reinterpret_cast<float*>(wsm + lo.fp_off);
-  const int64_t fbase = (int64_t)sid * nl;
   FootCol fc[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -265,32 +278,42 @@ __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& 
                               : FootCol{0, 1, 1, 0, 0, 0, 0, 0};
   }
   // 1. window origins, lane per (layer, axis): the first tap of the pupil index with the
-  //    smaller coordinate; then the stencil entries, lane per (layer, axis, pupil index),
-  //    from the launch's entry table of this frame
+  //    smaller coordinate (the first one: coordinates grow with the index); then the stencil
+  //    entries, lane per (layer, axis, pupil index), from the launch's entry table of this
+  //    frame.  Everything is loaded before anything is stored: one memory round trip.
   const FootEnt* ent =
       p.foot_ent + (int64_t)frame * p.foot_ent_per_frame + S.foot_ent_off;  // [nl][2][n_pup]
-  for (int e = lane; e < 2 * nl; e += kWave) {
-    const int i0 = (e & 1) ? sb.a * NS : sb.b * NS;
-    const double a = p.foot_axis[fbase * 2 + e].a;
-    forg[e] = ent[e * S.n_pup + (a >= 0.0 ? i0 : i0 + NS - 1)].i0;
-  }
-  wave_sync();
   {
-    const int lp = lane / TPL, j = lane - lp * TPL;
+    int org = 0;
+    if (lane < 2 * nl) org = ent[lane * S.n_pup + ((lane & 1) ? sb.a * NS : sb.b * NS)].i0;
+    const int lp = small_div<TPL>(lane), j = lane - lp * TPL;
     const int axis = j >= NS ? 1 : 0;
     const int idx = axis ? sb.a * NS + (j - NS) : sb.b * NS + j;
-    for (int l0 = 0; l0 < nl; l0 += LPP) {
-      const int l = l0 + lp;
-      if (lp < LPP && l < nl) {
-        const FootEnt E = ent[(2 * l + axis) * S.n_pup + idx];
-        FootTap t;
-        t.w0 = E.w0;  // rows: the projection kernel's ry.w0 * wl
-        t.w1 = E.w1;
-        t.k = E.k;  // byte offset in the window
-        tab[l * TPL + j] = t;
+    constexpr int kB = 4;  // passes in flight
+    for (int l0 = 0; l0 < nl; l0 += kB * LPP) {
+      FootEnt E[kB];
+#pragma unroll
+      for (int k = 0; k < kB; ++k) {
+        const int l = min(l0 + k * LPP + lp, nl - 1);
+        E[k] = ent[(2 * l + axis) * S.n_pup + idx];
+      }
+#pragma unroll
+      for (int k = 0; k < kB; ++k) {
+        const int l = l0 + k * LPP + lp;
+        if (lp < LPP && l < nl) {
+          FootTap t;
+          t.w0 = E[k].w0;  // rows: the projection kernel's ry.w0 * wl
+          t.w1 = E[k].w1;
+          t.k = E[k].k;  // byte offset in the window
+          tab[l * TPL + j] = t;
+        }
       }
     }
+    if (lane < 2 * nl) forg[lane] = org;
+    for (int e = lane + kWave; e < 2 * nl; e += kWave)
+      forg[e] = ent[e * S.n_pup + ((e & 1) ? sb.a * NS : sb.b * NS)].i0;
   }
+  wave_sync();
   // 2. window columns (32-bit byte offsets: the plan keeps every layer below 2^30 floats),
   // all ROWS rows of a column slot (rows fh.. of a slot are loaded and stored but never
   // read).  Rows leave the grid (wrap, or clamp on a zero-boundary grid) only for windows at
@@ -402,67 +425,42 @@ __device__ __forceinline__ void otf_field(const FwdParams& p, const DevSensor& S
   constexpr int PPL = (NPIX + kWave - 1) / kWave;  // pixels per lane
   const int lane = lane_id();
   const int nl = p.n_layers;
-  // small per-sensor tables -> LDS (consumed by the lag sums and the image stages); with a
-  // staged footprint they overlay the window, so they follow it
-  auto tables = [&]() {
-    float2* st = reinterpret_cast<float2*>(wsm + lo.stab_off);
-    float2* wt = reinterpret_cast<float2*>(wsm + lo.wtab_off);
-    for (int k = lane; k < 2 * NS - 1 + S.n_pix; k += kWave) {
-      if (k < 2 * NS - 1) st[k] = p.stab[S.stab_off + k];
-      else wt[k - (2 * NS - 1)] = p.wtab[S.wtab_off + k - (2 * NS - 1)];
-    }
-  };
-  if constexpr (FIELD != kFieldFoot) tables();
-  if constexpr (FIELD == kFieldFoot) {
+  OtfTables<NS> tables;
+  tables.load(p, S, sb);
+  if constexpr (FIELD != kFieldGather) {
     float ph[PPL];
-    foot_phase<NS>(p, S, sb, sid, b, frame, wsm, lo, ph);
-    wave_sync();  // E and the tables overlay the stencil entries and the window just read
-    tables();
+    if constexpr (FIELD == kFieldFoot) {
+      foot_phase<NS>(p, S, sb, b, frame, wsm, lo, ph);
+      wave_sync();  // E and the tables overlay the stencil entries and the window just read
+    } else {  // the projection kernel already wrote kappa psi
+      const float* src = p.phase_in + (int64_t)b * p.phase_per_real + S.phase_off +
+                         (int64_t)sb.v * NPIX;
+#pragma unroll
+      for (int i = 0; i < PPL; ++i) ph[i] = src[min(lane + i * kWave, NPIX - 1)];
+    }
+    tables.store(p, S, wsm, lo);
     float2* E = reinterpret_cast<float2*>(wsm + lo.e_off);
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
       const int q = lane + i * kWave;
       if (q < NPIX) {
-        const int r = q / NS, c = q - r * NS;
-        const uint8_t amp = p.mask[S.mask_off + (sb.a * NS + r) * S.n_pup + sb.b * NS + c];
+        const int r = small_div<NS>(q), c = q - r * NS;
         float turns = fmaf(ph[i], 0.15915494309189535f, -field_ramp(S, r, c));
         turns -= rintf(turns);
         float sn, cs;
         sincos_rev(turns, &sn, &cs);
-        E[r * Otf<NS>::kEP + c] = amp ? make_float2(cs, sn) : make_float2(0.0f, 0.0f);
-      }
-    }
-    wave_sync();
-  } else if constexpr (FIELD == kFieldPhase) {  // the projection kernel already wrote kappa psi
-    const float* ph = p.phase_in + (int64_t)b * p.phase_per_real + S.phase_off +
-                      (int64_t)sb.v * NPIX;
-    float2* E = reinterpret_cast<float2*>(wsm + lo.e_off);
-#pragma unroll
-    for (int i = 0; i < PPL; ++i) {
-      const int q = lane + i * kWave;
-      if (q < NPIX) {
-        const int r = q / NS, c = q - r * NS;
-        const uint8_t amp = p.mask[S.mask_off + (sb.a * NS + r) * S.n_pup + sb.b * NS + c];
-        float turns = fmaf(ph[q], 0.15915494309189535f, -field_ramp(S, r, c));
-        turns -= rintf(turns);
-        float sn, cs;
-        sincos_rev(turns, &sn, &cs);
-        E[r * Otf<NS>::kEP + c] = amp ? make_float2(cs, sn) : make_float2(0.0f, 0.0f);
+        E[q] = tables.amp[i] ? make_float2(cs, sn) : make_float2(0.0f, 0.0f);
       }
     }
     wave_sync();
   } else {
-    // amplitude of this lane's pixels (issued early)
-    uint8_t amp[PPL];
+    tables.store(p, S, wsm, lo);
     int pr[PPL], pc[PPL];
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
-      const int q = lane + i * kWave;
-      const int qq = q < NPIX ? q : 0;
-      pr[i] = qq / NS;
+      const int qq = min(lane + i * kWave, NPIX - 1);
+      pr[i] = small_div<NS>(qq);
       pc[i] = qq - pr[i] * NS;
-      amp[i] = q < NPIX ? p.mask[S.mask_off + (sb.a * NS + pr[i]) * S.n_pup + sb.b * NS + pc[i]]
-                        : 0;
     }
     // taps: [l][0..NS) columns, [l][NS..2NS) rows
     Tap* taps = reinterpret_cast<Tap*>(wsm + lo.taps_off);
@@ -530,152 +528,209 @@ __device__ __forceinline__ void otf_field(const FwdParams& p, const DevSensor& S
       float sn, cs;
       sincos_rev(turns, &sn, &cs);
       if (q < NPIX)
-        E[pr[i] * Otf<NS>::kEP + pc[i]] = amp[i] ? make_float2(cs, sn) : make_float2(0.0f, 0.0f);
+        E[q] = tables.amp[i] ? make_float2(cs, sn) : make_float2(0.0f, 0.0f);
     }
     wave_sync();
   }
 }
 
-// Lag sums of one round of row-pair jobs for the lag columns [IX0, IX0 + W) (held in the
-// partial-row region, kChunk columns per job), times the elongation and binning factors:
-// AW[dy][dx] (+)= w_dy Kel(dx, dy) s(dx) s(dy) sum_r part, lane per lag (dy, dx).
-template <int NS, int LP, int IX0, int W>
-__device__ __forceinline__ void otf_lagsum(const DevSensor& S, const DevSubap& sb,
-                                           const NaEntry& el, char* wsm, const OtfLds& lo,
-                                           int j0) {
-  constexpr int NL = Otf<NS>::kLags;
-  const int lane = lane_id();
-  const float2* part = reinterpret_cast<const float2*>(wsm + lo.part_off);
-  const float2* stab = reinterpret_cast<const float2*>(wsm + lo.stab_off);
-  float2* aw = reinterpret_cast<float2*>(wsm + lo.aw_off);
-  // weighted lag value at (dy, column ix) from the row sum a
-  auto weigh = [&](int dy, int ix, float2 a) {
-    const int dx = ix - (NS - 1);
-    const float2 sx = stab[ix], sy = stab[dy + NS - 1];
-    const float proj = fmaf((float)dx, sb.ex, (float)dy * sb.ey);
-    const float2 k = elong_tf(sb, el, proj, dy == 0 ? 1.0f : 2.0f);
-    const float sr = sx.x * sy.x - sx.y * sy.y, si = sx.x * sy.y + sx.y * sy.x;
-    const float tr = sr * k.x - si * k.y;
-    const float ti = sr * k.y + si * k.x;
-    return make_float2(a.x * tr - a.y * ti, a.x * ti + a.y * tr);
-  };
-  if constexpr (Otf<NS>::kRounds == 1) {
-    // every job in one round: lane per (pair of lag rows dy and NS-1-dy, column).  The two
-    // rows hold NS - dy and dy + 1 jobs, in NS + 1 consecutive slots, so each lane sums
-    // exactly NS + 1 partial rows.
-    constexpr int NQ = (NS + 1) / 2;
-    static_assert(NQ * W <= kWave, "one pass");
-    const int q = lane / W, k = lane - q * W;
-    if (q < NQ) {
-      const int dyA = q, dyB = NS - 1 - q, nA = NS - q;
-      const float2* rows = part + q * (NS + 1) * Otf<NS, LP>::kPS + k;  // the pair's slots
-      float2 a = make_float2(0.0f, 0.0f), bsum = make_float2(0.0f, 0.0f);
-#pragma unroll
-      for (int t = 0; t <= NS; ++t) {
-        const bool inA = t < nA;
-        const float2 v = rows[t * Otf<NS, LP>::kPS];
-        if (inA) {
-          a.x += v.x;
-          a.y += v.y;
-        } else {
-          bsum.x += v.x;
-          bsum.y += v.y;
-        }
-      }
-      aw[dyA * NL + IX0 + k] = weigh(dyA, IX0 + k, a);
-      if (dyB != dyA) aw[dyB * NL + IX0 + k] = weigh(dyB, IX0 + k, bsum);
-    }
-    wave_sync();
-    return;
-  }
-  const int j1 = j0 + Otf<NS>::kJobsPerRound;
-#pragma unroll
-  for (int o0 = 0; o0 < NS * W; o0 += kWave) {
-    const int o = o0 + lane;
-    if (o < NS * W) {
-      const int dy = o / W, k = o - dy * W, ix = IX0 + k;
-      const int base = job_base<NS>(dy);
-      const int r0 = max(0, j0 - base), r1 = min(NS - dy, j1 - base);
-      float2 a = make_float2(0.0f, 0.0f);
-#pragma unroll
-      for (int r = 0; r < NS; ++r) {
-        if (r >= r0 && r < r1) {
-          const float2 v = part[(base + r - j0) * Otf<NS, LP>::kPS + k];
-          a.x += v.x;
-          a.y += v.y;
-        }
-      }
-      float2 t = weigh(dy, ix, a);
-      const int oa = dy * NL + ix;
-      if (j0 > 0) {
-        const float2 prev = aw[oa];
-        t.x += prev.x;
-        t.y += prev.y;
-      }
-      aw[oa] = t;
-    }
-  }
-  wave_sync();
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+
+// a + b * w
+__device__ __forceinline__ float2 cfma(float2 b, float2 w, float2 a) {
+  return make_float2(fmaf(b.x, w.x, fmaf(-b.y, w.y, a.x)), fmaf(b.x, w.y, fmaf(b.y, w.x, a.y)));
 }
 
-// One round of autocorrelation row-pair jobs [j0, j0 + jobs per round), lag columns
-// [IX0, IX0 + W): lane per (dy, r) forms sum_c E[r][c] conj(E[r+dy][c+dx]) for those dx in
-// registers and leaves them in the partial-row region, then the lag sums over r.  Taking the
-// lag row in kOtfLagParts passes keeps the registers and the LDS region at that fraction of a
-// row per job, at the same number of multiply-adds.
-template <int NS, int LP, int IX0, int W>
-__device__ __forceinline__ void otf_corr_part(const DevSensor& S, const DevSubap& sb,
-                                              const NaEntry& el, char* wsm, const OtfLds& lo,
-                                              int j0) {
+__device__ __forceinline__ float2 cmul2(float2 b, float2 w) {
+  return make_float2(fmaf(b.x, w.x, -(b.y * w.y)), fmaf(b.x, w.y, b.y * w.x));
+}
+
+// X[q] = sum_s a[s] (-i)^{q s}, in place
+__device__ __forceinline__ void otf_dft4(float2 a[4]) {
+  const float2 s02 = make_float2(a[0].x + a[2].x, a[0].y + a[2].y);
+  const float2 d02 = make_float2(a[0].x - a[2].x, a[0].y - a[2].y);
+  const float2 s13 = make_float2(a[1].x + a[3].x, a[1].y + a[3].y);
+  const float2 d13 = make_float2(a[1].x - a[3].x, a[1].y - a[3].y);
+  a[0] = make_float2(s02.x + s13.x, s02.y + s13.y);
+  a[1] = make_float2(d02.x + d13.y, d02.y - d13.x);
+  a[2] = make_float2(s02.x - s13.x, s02.y - s13.y);
+  a[3] = make_float2(d02.x - d13.y, d02.y + d13.x);
+}
+
+// Sum of a over the two half-waves in lanes 0-31 and of b in lanes 32-63 (ROWS = 32), or of
+// a over the two 16-lane rows of each half in its first row and of b in its second (ROWS = 16).
+template <int ROWS>
+__device__ __forceinline__ float half_sums(float a, float b) {
+  const uint32_t ua = __builtin_bit_cast(uint32_t, a), ub = __builtin_bit_cast(uint32_t, b);
+  if constexpr (ROWS == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(ua, ub, false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+  }
+}
+
+// Weighted lags AW[dy][dx] = w_dy Kel(dx, dy) s(dx) s(dy) A[dy][dx], dy = 0 .. NS-1, dx =
+// -(NS-1) .. NS-1 (slot dx + 2 Q of a row), A[dy][dx] = sum E[r][c] conj(E[r+dy][c+dx]),
+// through the F-point DFT of the field rows:
+//   1. G[r][f] = sum_c E[r][c] e^{-2 pi i f c / F}: lane (r, k0) forms the four frequencies
+//      k0 + Q q of its row from the sums over c = s mod 4 and a 4-point DFT;
+//   2. C[dy][f] = sum_r G[r][f] conj(G[r+dy][f]): lane (f, group g) takes the first factors
+//      r = g mod kGroups, with its rows g + j in registers, so that every lane runs the same
+//      products (rows past the field are zero); the groups are added across the wave;
+//   3. A[dy][dx] = 1/F sum_f C[dy][f] e^{-2 pi i f dx / F}: lane (dy, k0) forms the lags
+//      congruent to k0 modulo Q as in 1, with the same twiddles, and weighs them.
+// The kernel is bound by vector issue: for n_sub = 10 a wave of the split field takes 702
+// vector instructions, where forming every row pair's lags directly (400 multiply-adds a lane,
+// a sum of 55 partial lag rows through LDS, then the weights) made it 986-1,000; busy cycles of a spot
+// launch of 128 realisations of six 80 x 80 LGS: -27 %; 100 frames of one, with the projection
+// in the waves: 1,176 -> 1,008 us.  The row DFTs on the matrix cores measured slower: FP32 matrix
+// instructions hold the vector units for 32 cycles each (16x16x4).
+template <int NS>
+__device__ __forceinline__ void otf_corr(const DevSubap& sb, const NaEntry& el, char* wsm,
+                                         const OtfLds& lo) {
+  using O = Otf<NS>;
+  constexpr int Q = O::kQ, F = O::kF, GR = O::kGroups, RQ = O::kRows * Q;
   const int lane = lane_id();
   const float2* E = reinterpret_cast<const float2*>(wsm + lo.e_off);
-  float2* part = reinterpret_cast<float2*>(wsm + lo.part_off);
-  int dy = 0, r = 0;
-  bool ok;
-  if constexpr (Otf<NS>::kRounds == 1) {
-    ok = lane < Otf<NS>::kSlots && slot_job<NS>(lane, dy, r);
-  } else {
-    const int j = j0 + lane;
-    ok = lane < Otf<NS>::kJobsPerRound && j < Otf<NS>::kJobs;
-    if (ok) job_of<NS>(j, dy, r);
+  float2* G = reinterpret_cast<float2*>(wsm + lo.g_off);
+  float2* C = reinterpret_cast<float2*>(wsm + lo.c_off);
+  float2* aw = reinterpret_cast<float2*>(wsm + lo.aw_off);
+  const float2* stab = reinterpret_cast<const float2*>(wsm + lo.stab_off);
+  constexpr int kM = (NS + 3) / 4;  // field columns per residue modulo 4
+  auto twiddles = [&](int k0, float2 w[kOtfTw]) {
+    const float4* t = reinterpret_cast<const float4*>(wsm + lo.tw_off) + k0 * (kOtfTw / 2);
+#pragma unroll
+    for (int i = 0; i < kOtfTw / 2; ++i) {
+      const float4 v = t[i];
+      w[2 * i] = make_float2(v.x, v.y);
+      w[2 * i + 1] = make_float2(v.z, v.w);
+    }
+  };
+  // 1. row transforms
+  constexpr int kU1 = (RQ + kWave - 1) / kWave;
+#pragma unroll
+  for (int it = 0; it < kU1; ++it) {
+    const int u = lane + it * kWave;
+    if (RQ % kWave == 0 || it + 1 < kU1 || u < RQ) {
+      const int r = small_div<Q>(u), k0 = u - r * Q;
+      float2 w[kOtfTw], a[4];
+      twiddles(k0, w);
+      const float2* e = E + (r < NS ? r : NS - 1) * NS;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        a[s] = s < NS ? e[s < NS ? s : 0] : make_float2(0.0f, 0.0f);
+#pragma unroll
+        for (int m = 1; m < kM; ++m)
+          if (s + 4 * m < NS) a[s] = cfma(e[s + 4 * m], w[m - 1], a[s]);
+        if (s > 0 && s < NS) a[s] = cmul2(a[s], w[4 + s]);
+      }
+      otf_dft4(a);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        G[q * RQ + u] = r < NS ? a[q] : make_float2(0.0f, 0.0f);
+    }
   }
-  if (ok) {
-    // the second row stays in registers; the first streams from LDS one pixel at a time
-    float2 e2[NS];
+  wave_sync();
+  {  // 2. row products
+    constexpr int GL = kWave / GR;  // lanes of a group
+    const int g = lane / GL, fl = lane - g * GL;
+    const int f = fl < F ? fl : 0;
+    const int q = small_div<Q>(f), k0 = f - q * Q;
+    float2 R[NS], acc[NS];
 #pragma unroll
-    for (int c = 0; c < NS; ++c) e2[c] = E[(r + dy) * Otf<NS>::kEP + c];
-    float2 acc[W];
+    for (int j = 0; j < NS; ++j) R[j] = G[q * RQ + (g + j) * Q + k0];
+    wave_sync();  // C overlays G
 #pragma unroll
-    for (int k = 0; k < W; ++k) acc[k] = make_float2(0.0f, 0.0f);
+    for (int r = 0; r < NS; r += GR)
 #pragma unroll
-    for (int c1 = 0; c1 < NS; ++c1) {
-      const float2 e1 = E[r * Otf<NS>::kEP + c1];
+      for (int dy = 0; r + dy < NS; ++dy) {
+        const float2 u = R[r], v = R[r + dy];
+        if (r == 0) {
+          acc[dy].x = fmaf(u.x, v.x, u.y * v.y);
+          acc[dy].y = dy == 0 ? 0.0f : fmaf(u.y, v.x, -(u.x * v.y));
+        } else {
+          acc[dy].x = fmaf(u.x, v.x, fmaf(u.y, v.y, acc[dy].x));
+          if (dy > 0) acc[dy].y = fmaf(u.y, v.x, fmaf(-u.x, v.y, acc[dy].y));
+        }
+      }
+    // lane group g ends with the sums of the lags dy = g kD .. g kD + kD - 1
+    constexpr int kD = (NS + GR - 1) / GR;
+    float2 t[kD];
 #pragma unroll
-      for (int c2 = 0; c2 < NS; ++c2) {
-        // E[r][c1] conj(E[r+dy][c2]) -> lag dx = c2 - c1, column c2 - c1 + NS - 1
-        const int k = c2 - c1 + NS - 1 - IX0;
-        if (k >= 0 && k < W) {
-          float2& a = acc[k];
-          a.x = fmaf(e1.x, e2[c2].x, fmaf(e1.y, e2[c2].y, a.x));
-          a.y = fmaf(e1.y, e2[c2].x, fmaf(-e1.x, e2[c2].y, a.y));
+    for (int i = 0; i < kD; ++i) {
+      auto at = [&](int grp) {
+        const int dy = grp * kD + i;
+        return dy < NS ? acc[dy < NS ? dy : 0] : make_float2(0.0f, 0.0f);
+      };
+      if constexpr (GR == 2) {
+        const float2 a = at(0), b = at(1);
+        t[i] = make_float2(half_sums<32>(a.x, b.x), half_sums<32>(a.y, b.y));
+      } else {  // groups 0, 1 in lanes 0-31 and 2, 3 in lanes 32-63
+        const float2 a = at(0), b = at(1), c = at(2), d = at(3);
+        t[i] = make_float2(half_sums<16>(half_sums<32>(a.x, c.x), half_sums<32>(b.x, d.x)),
+                           half_sums<16>(half_sums<32>(a.y, c.y), half_sums<32>(b.y, d.y)));
+      }
+    }
+    if (fl < F) {
+#pragma unroll
+      for (int i = 0; i < kD; ++i)
+        if (NS % GR == 0 || g * kD + i < NS) C[(g * kD + i) * O::kCP + fl] = t[i];
+    }
+  }
+  wave_sync();
+  // 3. lags and their weights
+  constexpr int kU3 = (NS * Q + kWave - 1) / kWave;
+#pragma unroll
+  for (int it = 0; it < kU3; ++it) {
+    const int u = lane + it * kWave;
+    if (u < NS * Q) {
+      const int dy = small_div<Q>(u);
+      int k0 = u - dy * Q;
+      asm volatile("" : "+v"(k0));  // read again, not held in registers across the products
+      float2 w[kOtfTw], a[4];
+      twiddles(k0, w);
+      const float4* c = reinterpret_cast<const float4*>(C + dy * O::kCP);
+#pragma unroll
+      for (int m = 0; m < Q; ++m) {
+        const float4 lo4 = c[2 * m], hi4 = c[2 * m + 1];
+        const float2 v[4] = {make_float2(lo4.x, lo4.y), make_float2(lo4.z, lo4.w),
+                             make_float2(hi4.x, hi4.y), make_float2(hi4.z, hi4.w)};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[s] = m == 0 ? v[s] : cfma(v[s], w[m - 1], a[s]);
+        // two steps of loads in flight: all of them would take 8 Q registers
+        if (m & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int s = 1; s < 4; ++s) a[s] = cmul2(a[s], w[4 + s]);
+      otf_dft4(a);
+      // a[q] is the lag dx = k0 + Q q (less F for q >= 2); slots outside the lags stay unread
+      const float2 sy = stab[dy + NS - 1];
+      const float scale = dy == 0 ? 1.0f / (float)F : 2.0f / (float)F;
+      const float yp = (float)dy * sb.ey;
+      if (el.n == 0 || sb.gam == 0.0f) {  // wave-uniform: one real Gaussian
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int dx = k0 + Q * (q < 2 ? q : q - 4);
+          const float2 sx = stab[min(max(dx, 1 - NS), NS - 1) + NS - 1];
+          const float proj = fmaf((float)dx, sb.ex, yp);
+          const float k = __expf(-sb.alpha * proj * proj) * scale;
+          const float2 tw = cmul2(sx, sy);
+          aw[dy * O::kAP + dx + 2 * Q] = cmul2(a[q], make_float2(tw.x * k, tw.y * k));
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int dx = k0 + Q * (q < 2 ? q : q - 4);
+          const float2 sx = stab[min(max(dx, 1 - NS), NS - 1) + NS - 1];
+          const float2 k = elong_tf(sb, el, fmaf((float)dx, sb.ex, yp), scale);
+          aw[dy * O::kAP + dx + 2 * Q] = cmul2(a[q], cmul2(cmul2(sx, sy), k));
         }
       }
     }
-#pragma unroll
-    for (int k = 0; k < W; ++k) part[lane * Otf<NS, LP>::kPS + k] = acc[k];
   }
   wave_sync();
-  otf_lagsum<NS, LP, IX0, W>(S, sb, el, wsm, lo, j0);
-}
-
-template <int NS, int LP, int IX0 = 0>
-__device__ __forceinline__ void otf_corr_round(const DevSensor& S, const DevSubap& sb,
-                                               const NaEntry& el, char* wsm, const OtfLds& lo,
-                                               int j0) {
-  constexpr int NL = Otf<NS, LP>::kLags, CW = Otf<NS, LP>::kChunk;
-  constexpr int W = IX0 + CW <= NL ? CW : NL - IX0;
-  otf_corr_part<NS, LP, IX0, W>(S, sb, el, wsm, lo, j0);
-  if constexpr (IX0 + W < NL) otf_corr_round<NS, LP, IX0 + W>(S, sb, el, wsm, lo, j0);
 }
 
 // Fold modulo n_pix: P[Ky][Kx] = sum over lags (dy, dx) = (Ky, Kx) mod n_pix of AW, lane per K.
@@ -696,7 +751,7 @@ __device__ __forceinline__ void otf_fold(const DevSensor& S, char* wsm, const Ot
       for (int c = 0; c < (NL + 7) / 8 + 1; ++c) {
         const int dx = dx0 + 8 * c;
         if (dy < NS && dx < NS) {
-          const float2 v = aw[dy * NL + dx + NS - 1];
+          const float2 v = aw[dy * Otf<NS>::kAP + dx + 2 * Otf<NS>::kQ];
           acc.x += v.x;
           acc.y += v.y;
         }
@@ -712,7 +767,7 @@ __device__ __forceinline__ void otf_fold(const DevSensor& S, char* wsm, const Ot
     float2 acc = make_float2(0.0f, 0.0f);
     for (int dy = Ky; dy < NS; dy += np) {
       for (int dx = dx0; dx < NS; dx += np) {
-        const float2 v = aw[dy * NL + dx + NS - 1];
+        const float2 v = aw[dy * Otf<NS>::kAP + dx + 2 * Otf<NS>::kQ];
         acc.x += v.x;
         acc.y += v.y;
       }
@@ -722,35 +777,48 @@ __device__ __forceinline__ void otf_fold(const DevSensor& S, char* wsm, const Ot
   wave_sync();
 }
 
-typedef float v4f_t __attribute__((ext_vector_type(4)));
-
 // B[q] = c Re sum_K P[K] W^{K.q} on the matrix cores (n_pix <= 8), as two real 16 x 16 x 16
 // products of four v_mfma_f32_16x16x4f32 each:  [Zr | Zi] = [Pr | Pi] F1 with
 // F1 = [[C, S], [-S, C]], then B = c F2 [Zr ; Zi] with F2 = [C | -S] (C, S: cosine and sine of
 // 2 pi (k n mod n_pix) / n_pix, per-sensor tables).  Operand layout: lane l supplies
 // A[l%16][l/16] and B[l/16][l%16]; accumulator i of lane l holds D[4 (l/16) + i][l%16].
-// The intermediate [Zr | Zi] goes through LDS over the P and Z regions.
-__device__ __forceinline__ void otf_image_mfma(const FwdParams& p, const DevSensor& S,
+// The intermediate [Zr | Zi] goes through LDS over the P and Z regions.  The lane's operands
+// are loaded before the fold that precedes the image (ImageOps).
+struct ImageOps {
+  float f1[4], f2[4];
+};
+
+__device__ __forceinline__ ImageOps image_ops(const FwdParams& p, const DevSensor& S) {
+  ImageOps o;
+  const int lane = lane_id();
+  const int r16 = lane & 15, kq = lane >> 4;
+  const float* F1 = p.mtab + max(S.mtab_off, 0);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    o.f1[s] = S.mtab_off >= 0 ? F1[(kq + 4 * s) * 16 + r16] : 0.0f;
+    o.f2[s] = S.mtab_off >= 0 ? F1[256 + r16 * 16 + kq + 4 * s] : 0.0f;
+  }
+  return o;
+}
+
+__device__ __forceinline__ void otf_image_mfma(const DevSensor& S, const ImageOps& ops,
                                                char* wsm, const OtfLds& lo) {
   const int lane = lane_id();
   const int np = S.n_pix;
   const int r16 = lane & 15, kq = lane >> 4;
-  const float* F1 = p.mtab + S.mtab_off;
-  const float* F2 = F1 + 256;
   const float2* P = reinterpret_cast<const float2*>(wsm + lo.p_off);
   float* D = reinterpret_cast<float*>(wsm + lo.p_off);  // [16][16]
   float* B = reinterpret_cast<float*>(wsm + lo.b_off);
-  float a[4], f[4];
+  float a[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     const int k = kq + 4 * s, kk = k & 7;
     const float2 v = (r16 < np && kk < np) ? P[r16 * np + kk] : make_float2(0.0f, 0.0f);
     a[s] = k < 8 ? v.x : v.y;
-    f[s] = F1[k * 16 + r16];
   }
   v4f_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], f[s], acc, 0, 0, 0);
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], ops.f1[s], acc, 0, 0, 0);
   wave_sync();
 #pragma unroll
   for (int i = 0; i < 4; ++i) D[(4 * kq + i) * 16 + r16] = acc[i];
@@ -758,12 +826,11 @@ __device__ __forceinline__ void otf_image_mfma(const FwdParams& p, const DevSens
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     const int k = kq + 4 * s;
-    f[s] = F2[r16 * 16 + k];
     a[s] = k < 8 ? D[k * 16 + (r16 & 7)] : D[(k - 8) * 16 + 8 + (r16 & 7)];
   }
   acc = (v4f_t){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f[s], a[s], acc, 0, 0, 0);
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ops.f2[s], a[s], acc, 0, 0, 0);
   wave_sync();
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -774,10 +841,10 @@ __device__ __forceinline__ void otf_image_mfma(const FwdParams& p, const DevSens
 }
 
 // B[q] = c Re sum_K P[K] W^{K.q}, separable through Z[Ky][qx] (W = e^{2 pi i / n_pix}).
-__device__ __forceinline__ void otf_image(const FwdParams& p, const DevSensor& S, char* wsm,
+__device__ __forceinline__ void otf_image(const DevSensor& S, const ImageOps& ops, char* wsm,
                                           const OtfLds& lo) {
   if (S.mtab_off >= 0) {
-    otf_image_mfma(p, S, wsm, lo);
+    otf_image_mfma(S, ops, wsm, lo);
     return;
   }
   const int lane = lane_id();
@@ -868,22 +935,19 @@ __device__ __forceinline__ void write_slopes(const FwdParams& p, const DevSensor
   }
 }
 
-// Binned noise-free (or noisy) image of one subaperture into the wave's B region (LP: passes
-// over each lag row, which sets the partial-row region of the layout `lo`).
-template <int NS, int FIELD, int LP = kOtfLagParts>
+// Binned noise-free (or noisy) image of one subaperture into the wave's B region.
+template <int NS, int FIELD>
 __device__ __forceinline__ void otf_spot(const FwdParams& p, const DevSensor& S,
                                          const DevSubap& sb, int sid, int b, int64_t step,
                                          char* wsm, const OtfLds& lo, int frame = 0) {
   otf_field<NS, FIELD>(p, S, sb, sid, b, (double)step, wsm, lo, frame);
-  const NaEntry el = na_entry(p, step);
-#pragma unroll
-  for (int rd = 0; rd < Otf<NS>::kRounds; ++rd)
-    otf_corr_round<NS, LP>(S, sb, el, wsm, lo, rd * Otf<NS>::kJobsPerRound);
+  otf_corr<NS>(sb, na_entry(p, step), wsm, lo);
+  const ImageOps ops = image_ops(p, S);
   otf_fold<NS>(S, wsm, lo);
-  otf_image(p, S, wsm, lo);
+  otf_image(S, ops, wsm, lo);
 }
 
-template <int NS, int FIELD, int LP = kOtfLagParts>
+template <int NS, int FIELD>
 __device__ void otf_subap(const FwdParams& p, int t, int64_t step, char* wsm, int frame = 0) {
   int b, sid, v;
   t = __builtin_amdgcn_readfirstlane(t);  // wave-uniform: per-subaperture data in SGPRs
@@ -891,10 +955,10 @@ __device__ void otf_subap(const FwdParams& p, int t, int64_t step, char* wsm, in
   const DevSensor S = cload(p.sen, sid);
   const DevSubap sb = cload(p.sub, S.valid_off + v);
   // the layout the host sized the launch with: the per-pixel gather holds its stencil taps
-  // in the union (the sensor tables follow whichever of taps, partial rows and image is last)
+  // in the union (the sensor tables follow whichever of its parts is last)
   const OtfLds lo = otf_lds_layout(NS, p.n_layers, S.n_pix, FIELD == kFieldGather,
-                                   FIELD == kFieldFoot ? S.foot_floats : 0, LP);
-  otf_spot<NS, FIELD, LP>(p, S, sb, sid, b, step, wsm, lo, frame);
+                                   FIELD == kFieldFoot ? S.foot_floats : 0);
+  otf_spot<NS, FIELD>(p, S, sb, sid, b, step, wsm, lo, frame);
   const Cog c = cog_sums(p, S, sid, b, v, step + p.noise_dstep,
                          reinterpret_cast<const float*>(wsm + lo.b_off));
   write_slopes(p, S, b, v, c, frame);

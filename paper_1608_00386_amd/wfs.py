@@ -160,8 +160,8 @@ class Plan:
         schedule: field is where a frame's spot waves get the phase ("gather", "split",
         "footprint"), frames how ``forward_steps`` runs ("sequential", "pipelined",
         "one_launch", "overlapped": the next frame projected on a second stream), fft_launch where FFT-path blocks run ("side_stream" or "same_launch"),
-        proj_rows the projection kernel's pupil rows per block, lag_passes the split field's
-        passes over each lag row (2 or 3)."""
+        proj_rows the projection kernel's pupil rows per block, lag_passes the value last set
+        (2 or 3; no kernel depends on it)."""
         v = [ctypes.c_int32() for _ in range(6)]
         L.check(self._lib.wfs_plan_schedule(self._h, *[ctypes.byref(x) for x in v]),
                 "wfs_plan_schedule")
