@@ -337,6 +337,8 @@ int recon_apply_noalloc(const float* R, int32_t M, int32_t N, const float* S, in
  *   interaction matrix transposed.  ref_slopes: device [n_slopes], realisation 0 of an
  *   unpoked batch at `step` (NULL = not wanted).  work: device, at least the number of floats
  *   wfs_calibrate_work returns.  Asynchronous on `stream`; deterministic for fixed inputs.
+ *   Where no sensor draws noise and the actuators are elements of zero-boundary grids, only
+ *   the subapertures a poke can reach are formed (the same rows, bit for bit).
  */
 int wfs_calibrate_work(wfs_plan_t plan, int64_t* work_floats);
 int wfs_calibrate(wfs_plan_t plan, const float* base, int64_t act_offset, int32_t n_act,

@@ -201,6 +201,17 @@ __device__ __forceinline__ void task_of(const TaskTable& tt, int t, int& b, int&
   v = r - tt.start[k];
 }
 
+// One layer element read with a value added to it (an actuator poke), or none: a compile-time
+// choice of the field and projection code.
+struct NoPoke {
+  static constexpr bool kOn = false;
+};
+struct Poke {
+  static constexpr bool kOn = true;
+  int32_t l, ix, iy;  // layer (-1: the element is in no layer), column, row
+  float delta;
+};
+
 // Time step of a launch: p.step, or the device counter plus p.step (graph replays).
 __device__ __forceinline__ int64_t current_step(const FwdParams& p) {
   return p.use_dev_step ? *p.step_dev + p.step : p.step;

@@ -1,6 +1,9 @@
-// Spot kernels of the forward model for subaperture size 10 (wfs_forward_kernels.h).
+// Spot kernels of the forward model (wfs_forward_kernels.h) and of the sparse calibration
+// (wfs_calib_kernels.h), subaperture size 10.
+#include "wfs_calib_kernels.h"
 #include "wfs_forward_kernels.h"
 
 namespace wfs {
 template hipError_t launch_fwd_ns<10>(const FwdParams&, hipStream_t);
+template hipError_t launch_calib_ns<10>(const FwdParams&, const CalibParams&, hipStream_t);
 }  // namespace wfs

@@ -195,6 +195,18 @@ struct SideStream {
   hipEvent_t fork = nullptr, join = nullptr;
 };
 
+// Sparse calibration (noise-free sensors, actuators of zero-boundary grids): only the
+// subapertures whose stencils can touch a poked element are formed.
+struct CalibParams {
+  int64_t act_offset;  // element of actuator 0 in a realisation's layer buffer
+  int32_t n_act;       // actuators of the launch
+  float amp;
+  float* im;           // row of the launch's actuator 0
+  int64_t ld_im;
+  int32_t cells;       // lag-domain launch: subapertures of a sensor a poke can touch, at most
+  int32_t per_act;     // lag-domain launch: cells x sensors
+};
+
 struct AdjParams {
   FwdParams f;              // forward tables (noise off)
   const float* grad_slopes; // [B][n_slopes]

@@ -256,9 +256,10 @@ struct FootTap {
 // Indices, weights and the order of every floating-point operation are those of the
 // projection kernel, so the phase (and everything after it) matches the split schedule bit
 // for bit.
-template <int NS>
+template <int NS, class PK>
 __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& S,
-                                           const DevSubap& sb, int b, int frame, char* wsm, const OtfLds& lo, float* ph) {
+                                           const DevSubap& sb, int b, int frame, char* wsm,
+                                           const OtfLds& lo, const PK& pk, float* ph) {
   constexpr int NPIX = NS * NS;
   constexpr int PPL = (NPIX + kWave - 1) / kWave;
   constexpr int ROWS = NS + 2;                   // window rows loaded per column
@@ -371,6 +372,11 @@ __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& 
       float* dst = fp + fc[k].dst;
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) dst[i] = val[k][i];
+      if constexpr (PK::kOn) {  // the lane that holds the poked element's column adds to it
+        const int l = fc[k].lj >> 8, row = pk.iy - oyv[k];
+        if (l == pk.l && cbase[k] == fc[k].offset + pk.ix && row >= 0 && row < fc[k].fh)
+          dst[row] += pk.delta;
+      }
     }
   }
   wave_sync();
@@ -417,10 +423,11 @@ __device__ __forceinline__ void foot_phase(const FwdParams& p, const DevSensor& 
 // Fills the wave's E region with the subaperture field E[r][c] = A exp(i(psi - pi (r+c)/N)),
 // and the wave's copies of the sensor's lag-phase and twiddle tables.  All per-subaperture
 // values (S, sb, sid, b) are wave-uniform.  FIELD says where the phase comes from.
-template <int NS, int FIELD>
+template <int NS, int FIELD, class PK = NoPoke>
 __device__ __forceinline__ void otf_field(const FwdParams& p, const DevSensor& S,
                                           const DevSubap& sb, int sid, int b, double stepd,
-                                          char* wsm, const OtfLds& lo, int frame = 0) {
+                                          char* wsm, const OtfLds& lo, int frame = 0,
+                                          const PK& pk = PK{}) {
   constexpr int NPIX = NS * NS;
   constexpr int PPL = (NPIX + kWave - 1) / kWave;  // pixels per lane
   const int lane = lane_id();
@@ -430,7 +437,7 @@ __device__ __forceinline__ void otf_field(const FwdParams& p, const DevSensor& S
   if constexpr (FIELD != kFieldGather) {
     float ph[PPL];
     if constexpr (FIELD == kFieldFoot) {
-      foot_phase<NS>(p, S, sb, b, frame, wsm, lo, ph);
+      foot_phase<NS>(p, S, sb, b, frame, wsm, lo, pk, ph);
       wave_sync();  // E and the tables overlay the stencil entries and the window just read
     } else {  // the projection kernel already wrote kappa psi
       const float* src = p.phase_in + (int64_t)b * p.phase_per_real + S.phase_off +
@@ -936,11 +943,12 @@ __device__ __forceinline__ void write_slopes(const FwdParams& p, const DevSensor
 }
 
 // Binned noise-free (or noisy) image of one subaperture into the wave's B region.
-template <int NS, int FIELD>
+template <int NS, int FIELD, class PK = NoPoke>
 __device__ __forceinline__ void otf_spot(const FwdParams& p, const DevSensor& S,
                                          const DevSubap& sb, int sid, int b, int64_t step,
-                                         char* wsm, const OtfLds& lo, int frame = 0) {
-  otf_field<NS, FIELD>(p, S, sb, sid, b, (double)step, wsm, lo, frame);
+                                         char* wsm, const OtfLds& lo, int frame = 0,
+                                         const PK& pk = PK{}) {
+  otf_field<NS, FIELD>(p, S, sb, sid, b, (double)step, wsm, lo, frame, pk);
   otf_corr<NS>(sb, na_entry(p, step), wsm, lo);
   const ImageOps ops = image_ops(p, S);
   otf_fold<NS>(S, wsm, lo);

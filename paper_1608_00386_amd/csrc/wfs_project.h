@@ -49,8 +49,10 @@ __device__ __forceinline__ void project_taps(const FwdParams& p, int sid, int ro
 
 // Phase sums of the thread's two pixels of row group g (rows ry0 and ry0 + kProjRows / 2 of
 // the block's row taps).
+template <class PK>
 __device__ __forceinline__ void project_pixels(const FwdParams& p, int b, int rows, int ry0,
-                                               const char* smem, float psi[2], const int tx) {
+                                               const char* smem, float psi[2], const int tx,
+                                               const PK& pk) {
   const int nl = p.n_layers;
   const Tap* ctap = reinterpret_cast<const Tap*>(smem);
   const Tap* rtap = ctap + nl * kProjStrip;
@@ -72,6 +74,23 @@ __device__ __forceinline__ void project_pixels(const FwdParams& p, int b, int ro
         v[jj][k][3] = ld_byte(gl, (uint32_t)(ry.i1 + cx.i1));
       }
     }
+    if constexpr (PK::kOn) {
+#pragma unroll
+      for (int jj = 0; jj < kProjLC; ++jj) {
+        const int l = min(l0 + jj, nl - 1);
+        if (l != pk.l) continue;
+        const Tap cx = ctap[l * kProjStrip + tx];
+        const int32_t hit = 4 * (pk.iy * cload(p.lay, l).nx + pk.ix);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const Tap ry = rtap[l * rows + ry0 + k * (kProjRows / 2)];
+          v[jj][k][0] = ry.i0 + cx.i0 == hit ? v[jj][k][0] + pk.delta : v[jj][k][0];
+          v[jj][k][1] = ry.i0 + cx.i1 == hit ? v[jj][k][1] + pk.delta : v[jj][k][1];
+          v[jj][k][2] = ry.i1 + cx.i0 == hit ? v[jj][k][2] + pk.delta : v[jj][k][2];
+          v[jj][k][3] = ry.i1 + cx.i1 == hit ? v[jj][k][3] + pk.delta : v[jj][k][3];
+        }
+      }
+    }
     // all loads of the chunk are issued; the weights are read again from LDS so that they
     // do not hold registers while the loads are in flight
     asm volatile("" ::: "memory");
@@ -91,8 +110,9 @@ __device__ __forceinline__ void project_pixels(const FwdParams& p, int b, int ro
   }
 }
 
+template <class PK = NoPoke>
 __device__ __forceinline__ void project_block(const FwdParams& p, int blk, float* phase,
-                                              double stepd, char* smem) {
+                                              double stepd, char* smem, const PK& pk = PK{}) {
   const int b = blk / p.proj_per_real;
   const int2 d = cload(p.proj_desc, blk - b * p.proj_per_real);
   const int sid = d.y & 0xFFFFFF;
@@ -117,7 +137,7 @@ __device__ __forceinline__ void project_block(const FwdParams& p, int blk, float
                     : -1;
     }
     float psi[2] = {0.0f, 0.0f};
-    project_pixels(p, b, rows, g + ty, smem, psi, tx);
+    project_pixels(p, b, rows, g + ty, smem, psi, tx, pk);
 #pragma unroll
     for (int k = 0; k < 2; ++k)
       if (vsub[k] >= 0)
