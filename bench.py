@@ -678,23 +678,23 @@ def main():
                      "of up to 256 frames, each after the small launch that fills its frames' "
                      "stencil entries; each wave projects its subaperture from a footprint "
                      "staged in LDS)")
-        traffic_key = "wfs_forward_kernel<10, 2, false, false>"
+        traffic_key = "wfs_forward_kernel<10, 2, false>"
     elif frames == "pipelined":
         kern_ms = (r1["gpu_ms_per_frame"] * args.steps - r1["project_ms"]) / args.steps
         kern_name = "wfs_forward_kernel<10, split> (spots of step k + projection of step k+1)"
-        traffic_key = "wfs_forward_kernel<10, 1, false, true>"
+        traffic_key = "wfs_forward_kernel<10, 1, true>"
     elif frames == "overlapped":  # projections run beside the spots: the spot launch alone
         kern_ms = r1["spots_ms"]
         kern_name = "wfs_forward_kernel<10, split> (spots; projections on a second stream)"
-        traffic_key = "wfs_forward_kernel<10, 1, false, false>"
+        traffic_key = "wfs_forward_kernel<10, 1, false>"
     elif field == "split":
         kern_ms = r1["gpu_ms_per_frame"] - r1["project_ms"]
         kern_name = "wfs_forward_kernel<10, split> (spots)"
-        traffic_key = "wfs_forward_kernel<10, 1, false, false>"
+        traffic_key = "wfs_forward_kernel<10, 1, false>"
     elif field == "footprint":
         kern_ms = r1["gpu_ms_per_frame"]
         kern_name = "wfs_forward_kernel<10, footprint> (one frame per launch)"
-        traffic_key = "wfs_forward_kernel<10, 2, false, false>"
+        traffic_key = "wfs_forward_kernel<10, 2, false>"
     else:
         kern_ms = r1["gpu_ms_per_frame"]
         kern_name = "wfs_forward_kernel<10, gather> (per-pixel gather)"

@@ -209,10 +209,8 @@ int wfs_spots(wfs_plan_t plan, const float* phase, int64_t step, uint64_t seed, 
  *   joins `stream`).  Fields 1 and 2 and frames 0-3 give the same bits;
  *   field 0 its own.  Field 2 for single frames needs a plan without FFT-path sensors.
  *   xcd_remap = 1 when blocks are renumbered so neighbouring tasks share an XCD.
- *   fft_launch (plans with both paths, fields 0 and 1): 0 = the FFT-path blocks run as a
- *   launch of their own on the plan's second stream, concurrently; 1 = they are blocks of
- *   the same launch as the lag-domain blocks (and, pipelined, the next step's projection:
- *   one launch per step).  proj_rows: the projection kernel's tile height, pupil rows per
+ *   fft_launch (plans with both paths): 0 = the FFT-path subapertures run on the plan's
+ *   second stream, beside the lag-domain launch; 1 = before it on the caller's stream.  proj_rows: the projection kernel's tile height, pupil rows per
  *   block (8, 16 or 32 where a block's layer taps fit 32 KiB of LDS; taller blocks share each
  *   column tap among more pixels, shorter ones give more blocks).  lag_passes: 2 or 3 as set by
  *   wfs_plan_set_schedule (2 at creation); kept for callers that pin it, no kernel depends on

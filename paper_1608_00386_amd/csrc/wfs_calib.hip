@@ -15,7 +15,6 @@
 #include <stdint.h>
 
 #include "wfs_calib_kernels.h"
-#include "wfs_fft.h"
 #include "wfs_project.h"
 
 namespace wfs {
@@ -34,11 +33,6 @@ __global__ __launch_bounds__(kCalBlock) void calib_fill_kernel(const float* __re
     d[k] = (s[k] - s[k]) / two_amp;
 }
 
-// FFT-path sensors, realisation b of the batch: actuator b / 2 at +amp (b even) or -amp.
-__device__ __forceinline__ Poke fft_poke(const FwdParams& p, const CalibParams& q, int b) {
-  return poke_at(p, q.act_offset + (b >> 1), b & 1 ? -q.amp : q.amp);
-}
-
 // Projection of the pixels of the touched FFT-path subapertures (blocks of wfs_project_kernel;
 // every realisation reads the same layers).
 __global__ __launch_bounds__(kBlock) void calib_project_kernel(FwdParams p, CalibParams q,
@@ -50,30 +44,13 @@ __global__ __launch_bounds__(kBlock) void calib_project_kernel(FwdParams p, Cali
   const int rows = kProjRows << (d.y >> 24);
   const double stepd = (double)current_step(p);
   const DevSensor S = cload(p.sen, sid);
-  const Poke pk = fft_poke(p, q, b);
+  const Poke pk = batch_poke(p, q, b);
   const SubRange r = sub_range(p, S, sid, pk, stepd);
   if (r.a0 > r.a1 || r.b0 > r.b1 || row0 >= (r.a1 + 1) * S.n_sub ||
       row0 + rows <= r.a0 * S.n_sub || c0 >= (r.b1 + 1) * S.n_sub ||
       c0 + kProjStrip <= r.b0 * S.n_sub)
     return;  // block-uniform
   project_block(p, blockIdx.x, phase, stepd, smem, pk);
-}
-
-// Spectrum chunks of the touched FFT-path subapertures, one per wave.
-__global__ __launch_bounds__(kBlock) void calib_fft_kernel(FwdParams p, CalibParams q) {
-  extern __shared__ __align__(16) char smem[];
-  const int w = threadIdx.x >> 6;
-  const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + w);
-  if (task >= p.fft.per_real * p.batch) return;
-  int b, sid, u;
-  task_of(p.fft, task, b, sid, u);
-  const DevSensor S = cload(p.sen, sid);
-  const int M = S.n_fft >= 32 ? 32 : S.n_fft, Q = S.n_fft / M;
-  const DevSubap sb = cload(p.sub, S.valid_off + u / (Q * Q));
-  const int64_t step = current_step(p);
-  const SubRange r = sub_range(p, S, sid, fft_poke(p, q, b), (double)step);
-  if (sb.a < r.a0 || sb.a > r.a1 || sb.b < r.b0 || sb.b > r.b1) return;
-  fft_wave(p, task, step, smem + w * p.lds_per_wave);
 }
 
 // Their entries: thread per (FFT-path sensor, subaperture), block row per actuator.
@@ -143,19 +120,20 @@ hipError_t calib_fill(const float* slopes, int32_t n_slopes, int32_t n_act, floa
   return hipSuccess;
 }
 
+hipError_t launch_fft_spots(const FwdParams& p, const FftTables& t, const CalibParams* cal,
+                            hipStream_t st);
+
 // Entries of the FFT-path sensors for the q.n_act actuators of a chunk: p.batch = 2 q.n_act
 // realisations, the sensors' projection blocks, p.phase_in = phase.
-hipError_t calib_fft(const FwdParams& p, const CalibParams& q, float* phase, int proj_lds,
-                     hipStream_t st) {
+hipError_t calib_fft(const FwdParams& p, const FftTables& t, const CalibParams& q, float* phase,
+                     int proj_lds, hipStream_t st) {
   const int64_t pb = (int64_t)p.proj_per_real * p.batch;
-  const int64_t fb = ((int64_t)p.fft.per_real * p.batch + kWavesPerBlock - 1) / kWavesPerBlock;
-  if (pb == 0 || fb == 0) return hipSuccess;
-  if (pb > 0x7FFFFFFF || fb > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (pb == 0) return hipSuccess;
+  if (pb > 0x7FFFFFFF) return hipErrorInvalidValue;
   calib_project_kernel<<<(unsigned)pb, kBlock, proj_lds, st>>>(p, q, phase);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  calib_fft_kernel<<<(unsigned)fb, kBlock, p.lds_per_wave * kWavesPerBlock, st>>>(p, q);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_fft_spots(p, t, &q, st)) != hipSuccess) return e;
   calib_fft_diff_kernel<<<(unsigned)q.n_act, kWave, 0, st>>>(p, q);
   return hipGetLastError();
 }

@@ -57,6 +57,18 @@ __device__ __forceinline__ SubRange sub_range(const FwdParams& p, const DevSenso
   return r;
 }
 
+// FFT-path sensors, realisation b of a chunk: actuator b / 2 at +amp (b even) or -amp.
+__device__ __forceinline__ Poke batch_poke(const FwdParams& p, const CalibParams& q, int b) {
+  return poke_at(p, q.act_offset + (b >> 1), b & 1 ? -q.amp : q.amp);
+}
+
+__device__ __forceinline__ bool poke_touches(const FwdParams& p, const CalibParams& q,
+                                             const DevSensor& S, const DevSubap& sb, int sid,
+                                             int b, double stepd) {
+  const SubRange r = sub_range(p, S, sid, batch_poke(p, q, b), stepd);
+  return sb.a >= r.a0 && sb.a <= r.a1 && sb.b >= r.b0 && sb.b <= r.b1;
+}
+
 // Block = two (actuator, sensor, cell) tasks, each a pair of waves (+a, -a).
 template <int NS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void

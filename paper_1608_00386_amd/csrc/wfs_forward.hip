@@ -7,6 +7,7 @@
 // gravity stage.
 
 #include <cmath>
+#include <mutex>
 
 #include "wfs_fft.h"
 #include "wfs_otf.h"
@@ -77,34 +78,64 @@ static hipError_t launch_forward_ns(const FwdParams& p, int ns, hipStream_t st) 
   }
 }
 
-// FFT-path and lag-domain subapertures: by default in two launches, since the FFT path's
-// registers and LDS would otherwise set the occupancy of every lag-domain wavefront.  The
-// FFT-path blocks (large fields, one workgroup each, 48 KB of LDS) and the lag-domain blocks
-// go to separate launches, so that the lag-domain waves keep their own occupancy; with a side
-// stream the FFT-path launch runs concurrently (fork after everything already queued on st,
-// join before anything queued after this call).  With fft_inline they share one launch.
-hipError_t launch_forward(const FwdParams& p, int ns, hipStream_t st, const SideStream* side) {
-  if (p.fft_inline || p.fft_blocks == 0 || (p.otf_blocks == 0 && p.proj_blocks == 0))
-    return launch_forward_ns(p, ns, st);
-  FwdParams a = p;
-  a.otf_blocks = 0;
-  a.proj_blocks = 0;
-  FwdParams c = p;
-  c.fft_blocks = 0;
-  c.lds_per_wave = p.lds_per_wave_otf;
-  hipError_t e;
-  if (side && side->stream) {
-    e = hipEventRecord(side->fork, st);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
-    if (e == hipSuccess) e = launch_forward_ns(a, ns, side->stream);
-    if (e == hipSuccess) e = launch_forward_ns(c, ns, st);
-    if (e == hipSuccess) e = hipEventRecord(side->join, side->stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join, 0);
-    return e;
+// FFT-path subapertures, one launch per chunk count present; `cal`: the sparse calibration's
+// realisations and only the subapertures their pokes touch.
+template <int Q, bool CAL>
+static hipError_t launch_fft_q(const FwdParams& p, const TaskTable& t, const CalibParams& cal,
+                               hipStream_t st) {
+  const int64_t tasks = (int64_t)t.per_real * p.batch;
+  if (tasks == 0) return hipSuccess;
+  if (tasks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if constexpr (Q == 1) {
+    hipLaunchKernelGGL((fft_whole_kernel<CAL>),
+                       dim3((unsigned)((tasks + kWavesPerBlock - 1) / kWavesPerBlock)),
+                       dim3(kBlock), fft_spot_lds(1), st, p, t, cal);
+  } else {
+    // the field and the waves' tiles hold more than the default 64 KB of LDS (Q = 4)
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    std::call_once(once, [] {
+      err = hipFuncSetAttribute((const void*)fft_spot_kernel<Q, CAL>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, fft_spot_lds(Q));
+    });
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((fft_spot_kernel<Q, CAL>), dim3((unsigned)tasks),
+                       dim3(fft_waves(Q) * kWave), fft_spot_lds(Q), st, p, t, cal);
   }
-  e = launch_forward_ns(a, ns, st);
-  if (e != hipSuccess) return e;
-  return launch_forward_ns(c, ns, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_fft_spots(const FwdParams& p, const FftTables& t, const CalibParams* cal,
+                            hipStream_t st) {
+  if (!t.any) return hipSuccess;
+  const CalibParams c = cal ? *cal : CalibParams{};
+  hipError_t e = cal ? launch_fft_q<1, true>(p, t.t[0], c, st)
+                     : launch_fft_q<1, false>(p, t.t[0], c, st);
+  if (e == hipSuccess)
+    e = cal ? launch_fft_q<2, true>(p, t.t[1], c, st) : launch_fft_q<2, false>(p, t.t[1], c, st);
+  if (e == hipSuccess)
+    e = cal ? launch_fft_q<4, true>(p, t.t[2], c, st) : launch_fft_q<4, false>(p, t.t[2], c, st);
+  return e;
+}
+
+// FFT-path and lag-domain subapertures are separate launches.  With a side stream the FFT-path
+// launch runs beside the other (fork after everything already queued on st, join before
+// anything queued after this call); with fft_inline, or without, it goes first on st.
+hipError_t launch_forward(const FwdParams& p, int ns, const FftTables* fft, hipStream_t st,
+                          const SideStream* side) {
+  if (!fft || !fft->any) return launch_forward_ns(p, ns, st);
+  hipError_t e;
+  if (p.fft_inline || !side || !side->stream) {
+    e = launch_fft_spots(p, *fft, nullptr, st);
+    return e == hipSuccess ? launch_forward_ns(p, ns, st) : e;
+  }
+  e = hipEventRecord(side->fork, st);
+  if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
+  if (e == hipSuccess) e = launch_fft_spots(p, *fft, nullptr, side->stream);
+  if (e == hipSuccess) e = launch_forward_ns(p, ns, st);
+  if (e == hipSuccess) e = hipEventRecord(side->join, side->stream);
+  if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join, 0);
+  return e;
 }
 
 int foot_pitch(int ns) { return (ns + 2) | 1; }
@@ -161,5 +192,4 @@ hipError_t launch_step(int64_t* step_dev, int64_t value, int add, hipStream_t st
 
 namespace wfs {
 bool fft_supported(int n_sub, int n_fft, int bin) { return fft_supported_impl(n_sub, n_fft, bin); }
-int fft_wave_lds_bytes(int n_fft, int n_pix) { return fft_wave_lds_bytes_impl(n_fft, n_pix); }
 }  // namespace wfs

@@ -1,16 +1,13 @@
-// The spot launch of the forward model, one kernel per (subaperture size, mode): every sensor
-// of a plan for every realisation at one time step.
-//   blocks [0, fft_blocks)   : FFT path, one spectrum chunk of a large field per wave
-//   remaining blocks         : lag-domain path, one subaperture per 64-lane wavefront at a time,
-//                              with (pipelined frames) the next step's projection blocks spread
-//                              evenly among them
+// The spot launch of the forward model, one kernel per (subaperture size, mode): every
+// lag-domain sensor of that size for every realisation at one time step:
+// lag-domain path, one subaperture per 64-lane wavefront, with (pipelined frames) the next
+// step's projection blocks spread evenly among its blocks.
 // The mode is a template parameter so that each kernel only holds the registers of its own
-// paths: FIELD says where the lag-domain waves get the phase (kField*), FFT adds the FFT-path
-// blocks, PROJ the projection blocks.  With the staged footprint (kFieldFoot) one launch can
+// paths: FIELD says where the lag-domain waves get the phase (kField*), PROJ adds the
+// projection blocks.  With the staged footprint (kFieldFoot) one launch can
 // cover several frames: the lag-domain blocks repeat once per frame, frame k at step + k.
 #pragma once
 
-#include "wfs_fft.h"
 #include "wfs_otf.h"
 #include "wfs_project.h"
 
@@ -18,30 +15,19 @@ namespace wfs {
 
 // Register budget of the lag-domain kernels (waves per SIMD): the split field's LDS (4.4 KB
 // per wave at n_sub = 10) lets 8 four-wave blocks share a CU, the staged footprint's 5.
-template <int NS, int FIELD, bool PROJ>
+template <int FIELD, bool PROJ>
 constexpr int otf_waves_per_simd() {
   return FIELD == kFieldFoot || PROJ ? 6 : 8;
 }
 
-template <int NS, int FIELD, bool FFT, bool PROJ>
+template <int NS, int FIELD, bool PROJ>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu((FIELD == kFieldGather || FFT) ? 1
-                                                                  : otf_waves_per_simd<NS, FIELD, PROJ>())))
-void wfs_forward_kernel(
-    FwdParams p) {
+__attribute__((amdgpu_waves_per_eu(FIELD == kFieldGather ? 1 : otf_waves_per_simd<FIELD, PROJ>())))
+void wfs_forward_kernel(FwdParams p) {
   extern __shared__ __align__(16) char smem[];
   const int64_t step = current_step(p);
-  const int i = blockIdx.x;
-  if constexpr (FFT) {
-    if (i < p.fft_blocks) {  // FFT path: one spectrum chunk per wave
-      const int w = threadIdx.x >> 6;
-      fft_wave(p, i * kWavesPerBlock + w, step, smem + w * p.lds_per_wave);
-      return;
-    }
-  }
-  const int n = gridDim.x - p.fft_blocks;
-  const int ib = i - p.fft_blocks;
-  int L = p.xcd_remap ? xcd_logical_block(ib, n) : ib;
+  const int n = gridDim.x;
+  int L = p.xcd_remap ? xcd_logical_block(blockIdx.x, n) : blockIdx.x;
   if constexpr (PROJ) {
     // pipelined frames: projection blocks of the next step spread evenly among the spot
     // blocks, so memory-latency-bound gathers share the CUs with VALU-bound spot waves.
@@ -68,10 +54,9 @@ void wfs_forward_kernel(
   if (t < total) otf_subap<NS, FIELD>(p, t, step + frame, wsm, frame);
 }
 
-template <int NS, int FIELD, bool FFT, bool PROJ>
+template <int NS, int FIELD, bool PROJ>
 static hipError_t launch_fwd_mode(const FwdParams& p, int grid, int lds, hipStream_t st) {
-  hipLaunchKernelGGL((wfs_forward_kernel<NS, FIELD, FFT, PROJ>), dim3(grid), dim3(kBlock),
-                     lds, st, p);
+  hipLaunchKernelGGL((wfs_forward_kernel<NS, FIELD, PROJ>), dim3(grid), dim3(kBlock), lds, st, p);
   return hipGetLastError();
 }
 
@@ -79,29 +64,23 @@ static hipError_t launch_fwd_mode(const FwdParams& p, int grid, int lds, hipStre
 template <int NS>
 hipError_t launch_fwd_ns(const FwdParams& p, hipStream_t st) {
   const bool foot = p.otf_from_phase == kFieldFoot;
-  const int64_t grid64 = (int64_t)p.fft_blocks + p.proj_blocks +
-                         (int64_t)p.otf_blocks * (foot ? p.n_frames : 1);
+  const int64_t grid64 = (int64_t)p.proj_blocks + (int64_t)p.otf_blocks * (foot ? p.n_frames : 1);
   if (grid64 == 0) return hipSuccess;
   if (grid64 > 0x7FFFFFFF) return hipErrorInvalidValue;
   const int grid = (int)grid64;
   int lds = p.lds_per_wave * kWavesPerBlock;
   if (p.proj_blocks > 0 && p.proj_lds > lds) lds = p.proj_lds;
-  const bool fused = p.otf_from_phase == kFieldGather, fft = p.fft_blocks > 0,
-             proj = p.proj_blocks > 0;
-  if (foot) {  // one launch for every frame; no FFT-path or projection blocks
-    if (fft || proj || p.n_frames < 1) return hipErrorInvalidValue;
-    return launch_fwd_mode<NS, kFieldFoot, false, false>(p, grid, lds, st);
+  const bool fused = p.otf_from_phase == kFieldGather, proj = p.proj_blocks > 0;
+  if (foot) {  // one launch for every frame; no projection blocks
+    if (proj || p.n_frames < 1) return hipErrorInvalidValue;
+    return launch_fwd_mode<NS, kFieldFoot, false>(p, grid, lds, st);
   }
   if (fused) {  // the pipelined projection only exists in the split schedule
     if (proj) return hipErrorInvalidValue;
-    return fft ? launch_fwd_mode<NS, kFieldGather, true, false>(p, grid, lds, st)
-               : launch_fwd_mode<NS, kFieldGather, false, false>(p, grid, lds, st);
+    return launch_fwd_mode<NS, kFieldGather, false>(p, grid, lds, st);
   }
-  if (fft)
-    return proj ? launch_fwd_mode<NS, kFieldPhase, true, true>(p, grid, lds, st)
-                : launch_fwd_mode<NS, kFieldPhase, true, false>(p, grid, lds, st);
-  return proj ? launch_fwd_mode<NS, kFieldPhase, false, true>(p, grid, lds, st)
-              : launch_fwd_mode<NS, kFieldPhase, false, false>(p, grid, lds, st);
+  return proj ? launch_fwd_mode<NS, kFieldPhase, true>(p, grid, lds, st)
+              : launch_fwd_mode<NS, kFieldPhase, false>(p, grid, lds, st);
 }
 
 }  // namespace wfs

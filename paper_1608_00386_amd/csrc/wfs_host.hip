@@ -17,7 +17,10 @@
 #include "wfs_internal.h"
 
 namespace wfs {
-hipError_t launch_forward(const FwdParams& p, int ns, hipStream_t st, const SideStream* side);
+hipError_t launch_forward(const FwdParams& p, int ns, const FftTables* fft, hipStream_t st,
+                          const SideStream* side);
+hipError_t launch_fft_spots(const FwdParams& p, const FftTables& t, const CalibParams* cal,
+                            hipStream_t st);
 hipError_t launch_foot_entries(const FwdParams& p, FootEnt* out, int n_frames, hipStream_t st);
 hipError_t launch_project(const FwdParams& p, float* phase, int lds, hipStream_t st);
 int project_lds_bytes(int n_layers, int rows);
@@ -53,14 +56,13 @@ hipError_t calib_diff(const float* slopes, int32_t h, int32_t n_slopes, int32_t 
                       float amp, float* im, int64_t ld_im, hipStream_t st);
 hipError_t calib_fill(const float* slopes, int32_t n_slopes, int32_t n_act, float amp, float* im,
                       int64_t ld_im, hipStream_t st);
-hipError_t calib_fft(const FwdParams& p, const CalibParams& q, float* phase, int proj_lds,
-                     hipStream_t st);
+hipError_t calib_fft(const FwdParams& p, const FftTables& t, const CalibParams& q, float* phase,
+                     int proj_lds, hipStream_t st);
 hipError_t calib_spots(const FwdParams& p, int ns, const CalibParams& q, hipStream_t st);
 int otf_lds_bytes(int ns, int n_layers, int n_pix, bool with_taps, int foot_floats);
 int otf_twiddle_count(int ns);
 void otf_fill_twiddles(int ns, float2* out);
 int foot_pitch(int ns);
-int fft_wave_lds_bytes(int n_fft, int n_pix);
 bool fft_supported(int n_sub, int n_fft, int bin);
 }  // namespace wfs
 
@@ -164,7 +166,6 @@ struct wfs_plan_s {
   int2* d_adj_tab = nullptr;  // allocated on the first gather call, with d_gimg
   bool adj_clear_grad = true;  // the layer grids leave gaps inside the stride
   int lds_split = 0, lds_fused = 0;  // LDS bytes per lag-domain wave, per schedule
-  int lds_split_otf = 0, lds_fused_otf = 0;  // same, in a launch without FFT-path blocks
   int lag_passes = 2;        // wfs_plan_set_schedule's value, reported back
   int proj_lds = 0;          // bytes of LDS per projection block (all sensors)
   int proj_lds_fft = 0;      // same, FFT-path sensors only
@@ -197,9 +198,9 @@ struct wfs_plan_s {
   float* d_adj_fwd = nullptr;    // noise-free forward outputs it needs ([B][n_slopes + n_valid])
   int64_t fft_adj_per_real = 0;  // (both allocated on the first adjoint call)
   int fft_adj_lds = 0;           // LDS bytes per FFT-path adjoint wave
-  float* d_fft_part = nullptr;   // FFT path: partial images of the spectrum chunks
-  int32_t* d_fft_cnt = nullptr;  // and per-subaperture chunk counters (zero between launches)
-  int64_t fft_part_per_real = 0, fft_cnt_per_real = 0;
+  int32_t* d_fft_cnt = nullptr;  // FFT-path adjoint: per-subaperture chunk counters (zero
+  int64_t fft_cnt_per_real = 0;  // between launches)
+  FftTables fft_tab{};           // FFT-path sensors of the forward, by chunks per axis
   float4* d_na = nullptr;    // sodium-profile table (wfs_plan_na_profile), capacity na_cap
   int64_t na_cap = 0;
   std::vector<float4*> na_retired;  // outgrown tables: graphs captured earlier may hold them
@@ -689,12 +690,11 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     }
     P->adj_clear_grad = gap || end < layer_stride;
   }
-  // FFT path with several spectrum chunks: per realisation, every such sensor's partial
-  // images (Q^2 chunks of M x M floats = n_fft^2 per subaperture) and chunk counters
+  // FFT path with several spectrum chunks: chunk counters and partial buffers of the adjoint
+  // (fft_part: spectrum samples of a realisation, bounded)
   int64_t fft_part = 0, fft_cnt = 0, fft_adj = 0;
   for (int s : fft_ids) {
     const int N = sensors[s].n_fft, M = N >= 32 ? 32 : N, Q = N / M;
-    ds[s].fft_part_off = (int32_t)std::min<int64_t>(fft_part, (1LL << 31) - 1);
     ds[s].fft_cnt_off = (int32_t)fft_cnt;
     ds[s].fft_adj_off = (int32_t)std::min<int64_t>(fft_adj, (1LL << 31) - 1);
     if (Q > 1) {
@@ -710,7 +710,6 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     delete P;
     return fail(WFS_EINVAL, "wfs_plan: FFT-path partial images too large");
   }
-  P->fft_part_per_real = fft_part;
   P->fft_cnt_per_real = fft_cnt;
   // Projection tile heights: G groups of project_rows() rows per block, G = 1, 2, 4 where a
   // block's taps fit 32 KiB of LDS (taller blocks share each column tap among more pixels).
@@ -913,6 +912,14 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
       units[s] = P->n_valid[s] * Q * Q;
     }
     fill_tasks(b.fft, fft_ids, units);
+    for (int i = 0; i < 3; ++i) {  // forward: one task per subaperture
+      std::vector<int> ids;
+      for (int s : fft_ids)
+        if (sensors[s].n_fft / (sensors[s].n_fft >= 32 ? 32 : sensors[s].n_fft) == 1 << i)
+          ids.push_back(s);
+      fill_tasks(P->fft_tab.t[i], ids, P->n_valid);
+    }
+    P->fft_tab.any = !fft_ids.empty();
   }
   set_proj(b, P->proj_all);
   b.phase_per_real = P->phase_per_real;
@@ -939,18 +946,13 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     delete P;
     return fail(WFS_EINVAL, "wfs_plan: too many subaperture tasks");
   }
-  // LDS: lag-domain waves and FFT workgroups share one dynamic allocation; the split
-  // schedule's waves need no tap region (the fused gather does)
-  int lds_fft = 0;  // per FFT-path wave
-  for (int s : fft_ids)
-    lds_fft = std::max(lds_fft, fft_wave_lds_bytes(sensors[s].n_fft,
-                                                   sensors[s].n_fft / sensors[s].bin));
-  auto wave_lds = [&](bool taps, bool with_fft) {
-    int w = otf_ns ? otf_lds_bytes(otf_ns, n_layers, P->otf_max_npix, taps, 0) : 0;
-    if (with_fft) w = std::max(w, lds_fft);
+  // LDS of the lag-domain waves (group 0); the split schedule's need no tap region (the fused
+  // gather's do)
+  auto wave_lds = [&](bool taps) {
+    const int w = otf_ns ? otf_lds_bytes(otf_ns, n_layers, P->otf_max_npix, taps, 0) : 0;
     return std::max(16, (w + 15) & ~15);
   };
-  const int lds_wave = wave_lds(true, true);
+  const int lds_wave = wave_lds(true);
   if (lds_wave * kWavesPerBlock > 65536) {
     (void)hipFree(P->d_blob);
     delete P;
@@ -958,10 +960,8 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
                 lds_wave * kWavesPerBlock);
   }
   P->lds_fused = lds_wave;
-  P->lds_split = wave_lds(false, true);
-  P->lds_split_otf = wave_lds(false, false);
-  // every group's LDS per wave, in launches without FFT-path blocks (group 0's launch with
-  // them takes the larger figures above)
+  P->lds_split = wave_lds(false);
+  // every group's LDS per wave
   bool adj_ok = true;
   for (OtfGroup& G : P->groups) {
     auto r16 = [](int x) { return std::max(16, (x + 15) & ~15); };
@@ -999,13 +999,9 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     b.foot_ent = P->d_foot_ent;
     b.foot_ent_per_frame = (int32_t)foot_ent;
   }
-  P->lds_fused_otf = wave_lds(true, false);
   b.lds_per_wave = P->lds_split;
-  b.lds_per_wave_otf = P->lds_split_otf;
   P->adj_lds_per_wave = otf_ns ? P->groups[0].lds_adj : 16;
   if (!adj_ok) P->adj_lds_per_wave = 0;  // adjoint unsupported
-  // FFT blocks first, padded to a multiple of 8 so the lag-domain blocks keep their XCD order
-  b.fft_blocks = (int32_t)((P->fft_tasks + kWavesPerBlock - 1) / kWavesPerBlock);
   default_schedule(P);
   if (P->phase_per_real > 0) {
     const size_t n = (size_t)P->phase_per_real * batch;
@@ -1037,27 +1033,20 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     delete P;
     return fail(WFS_EUNSUPPORTED, "wfs_plan: projection taps of an FFT-path sensor exceed 64 KiB");
   }
-  if (P->fft_cnt_per_real > 0) {  // chunk partials and counters (counters start at zero)
-    e = hipMalloc((void**)&P->d_fft_part,
-                  sizeof(float) * (size_t)P->fft_part_per_real * P->batch);
-    if (e == hipSuccess)
-      e = hipMalloc((void**)&P->d_fft_cnt,
-                    sizeof(int32_t) * (size_t)P->fft_cnt_per_real * P->batch);
-    if (e == hipSuccess)
-      e = hipMemset(P->d_fft_cnt, 0, sizeof(int32_t) * (size_t)P->fft_cnt_per_real * P->batch);
+  if (P->fft_cnt_per_real > 0) {  // the adjoint's chunk counters (zero between launches)
+    const size_t bytes = sizeof(int32_t) * (size_t)P->fft_cnt_per_real * P->batch;
+    e = hipMalloc((void**)&P->d_fft_cnt, bytes);
+    if (e == hipSuccess) e = hipMemset(P->d_fft_cnt, 0, bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
-      if (P->d_fft_part) (void)hipFree(P->d_fft_part);
-  if (P->d_foot_ent) (void)hipFree(P->d_foot_ent);
+      if (P->d_foot_ent) (void)hipFree(P->d_foot_ent);
       if (P->d_fft_cnt) (void)hipFree(P->d_fft_cnt);
       (void)hipFree(P->d_blob);
       if (P->d_phase) (void)hipFree(P->d_phase);
       delete P;
-      return hip_fail(e, "wfs_plan: FFT-path chunk buffers");
+      return hip_fail(e, "wfs_plan: FFT-path chunk counters");
     }
-    P->base.fft_part = P->d_fft_part;
     P->base.fft_cnt = P->d_fft_cnt;
-    P->base.fft_part_per_real = P->fft_part_per_real;
     P->base.fft_cnt_per_real = (int32_t)P->fft_cnt_per_real;
   }
   if (P->d_phase) {  // overlapped frames: the projection stream and its events
@@ -1071,7 +1060,6 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
       destroy_ovl(P);
       (void)hipFree(P->d_blob);
       (void)hipFree(P->d_phase);
-      if (P->d_fft_part) (void)hipFree(P->d_fft_part);
       if (P->d_fft_cnt) (void)hipFree(P->d_fft_cnt);
       delete P;
       return hip_fail(e, "wfs_plan: projection stream");
@@ -1088,7 +1076,6 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
       destroy_ovl(P);
       (void)hipFree(P->d_blob);
       if (P->d_phase) (void)hipFree(P->d_phase);
-      if (P->d_fft_part) (void)hipFree(P->d_fft_part);
       if (P->d_fft_cnt) (void)hipFree(P->d_fft_cnt);
       delete P;
       return hip_fail(e, "wfs_plan: side stream");
@@ -1124,7 +1111,6 @@ int wfs_plan_destroy(wfs_plan_t P) {
   if (P->d_gimg) (void)hipFree(P->d_gimg);
   if (P->d_na) (void)hipFree(P->d_na);
   if (P->d_adj_tab) (void)hipFree(P->d_adj_tab);
-  if (P->d_fft_part) (void)hipFree(P->d_fft_part);
   if (P->d_fft_cnt) (void)hipFree(P->d_fft_cnt);
   if (P->d_fft_adj) (void)hipFree(P->d_fft_adj);
   if (P->d_adj_fwd) (void)hipFree(P->d_adj_fwd);
@@ -1231,24 +1217,24 @@ static int32_t blocks_of(const TaskTable& t, int32_t batch) {
 }
 
 // The spot launch of every lag-domain group (subaperture size) for `p`, which is set up for
-// group 0 (its tasks and LDS per wave, the FFT-path and projection blocks); the other groups
-// follow on `st` with their own tasks and LDS and neither FFT-path nor projection blocks.
+// group 0 (its tasks and LDS per wave, the projection blocks), the FFT-path sensors' (fft)
+// beside it; the other groups follow on `st` with their own tasks and LDS and no projection
+// blocks.
 static hipError_t launch_groups(wfs_plan_t P, const FwdParams& p, hipStream_t st,
-                                const SideStream* side) {
-  hipError_t e = launch_forward(p, P->otf_ns ? P->otf_ns : 2, st, side);
+                                bool fft = true) {
+  hipError_t e = launch_forward(p, P->otf_ns ? P->otf_ns : 2, fft ? &P->fft_tab : nullptr, st,
+                                &P->side);
   for (size_t g = 1; g < P->groups.size() && e == hipSuccess; ++g) {
     const OtfGroup& G = P->groups[g];
     FwdParams q = p;
     q.otf = G.tasks;
     q.otf_tw = G.otf_tw;
     q.otf_blocks = blocks_of(G.tasks, p.batch);
-    q.fft_blocks = 0;
     q.proj_blocks = 0;
     q.lds_per_wave = p.otf_from_phase == 2   ? G.lds_foot
                      : p.otf_from_phase == 1 ? G.lds_split
                                              : G.lds_fused;
-    q.lds_per_wave_otf = q.lds_per_wave;
-    e = launch_forward(q, G.ns, st, nullptr);
+    e = launch_forward(q, G.ns, nullptr, st, nullptr);
   }
   return e;
 }
@@ -1259,10 +1245,9 @@ static hipError_t launch_fwd_modes(wfs_plan_t P, FwdParams p, hipStream_t st) {
     p.otf_from_phase = 2;
     p.n_frames = 1;
     p.lds_per_wave = P->lds_foot;
-    p.lds_per_wave_otf = P->lds_foot;
     hipError_t e = launch_foot_entries(p, P->d_foot_ent, 1, st);
     if (e != hipSuccess) return e;
-    return launch_groups(P, p, st, &P->side);
+    return launch_groups(P, p, st);
   }
   const bool split = P->split && P->d_phase;
   if (split || P->fft_tasks > 0) {  // FFT-path sensors always read the projected phase
@@ -1273,8 +1258,7 @@ static hipError_t launch_fwd_modes(wfs_plan_t P, FwdParams p, hipStream_t st) {
   }
   p.otf_from_phase = split ? 1 : 0;
   p.lds_per_wave = split ? P->lds_split : P->lds_fused;
-  p.lds_per_wave_otf = split ? P->lds_split_otf : P->lds_fused_otf;
-  return launch_groups(P, p, st, &P->side);
+  return launch_groups(P, p, st);
 }
 
 int wfs_forward(wfs_plan_t P, const float* layers, int64_t step, uint64_t seed, float* slopes,
@@ -1321,15 +1305,13 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       q.otf_from_phase = 2;
       q.n_frames = std::min(P->foot_ent_cap, n - c0);
       q.lds_per_wave = P->lds_foot;
-      q.lds_per_wave_otf = P->lds_foot;
-      q.fft_blocks = 0;
       ef = launch_foot_entries(q, P->d_foot_ent, q.n_frames, st);
-      if (ef == hipSuccess) ef = launch_groups(P, q, st, nullptr);
+      if (ef == hipSuccess) ef = launch_groups(P, q, st, false);
     }
     return ef;
   };
   if (frames == 2) {
-    if (P->base.fft_blocks == 0) return foot_frames();
+    if (!P->fft_tab.any) return foot_frames();
     // FFT-path sensors read the projected phase: frame by frame on the side stream (their
     // projection into the plan's phase buffer, then their launch), concurrently with the one
     // footprint launch of every lag-domain frame on st
@@ -1344,11 +1326,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       e = launch_project(a, P->d_phase, P->proj_lds_fft, fs);
       if (e != hipSuccess) break;
       a.phase_in = P->d_phase;
-      a.otf_from_phase = 1;
-      a.otf_blocks = 0;
-      a.proj_blocks = 0;
-      a.lds_per_wave = P->lds_split;
-      e = launch_forward(a, P->otf_ns ? P->otf_ns : 2, fs, nullptr);
+      e = launch_fft_spots(a, P->fft_tab, nullptr, fs);
     }
     if (e == hipSuccess) e = foot_frames();
     if (e == hipSuccess && fs != st) {
@@ -1383,8 +1361,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       p.otf_from_phase = 1;
       p.proj_blocks = 0;
       p.lds_per_wave = P->lds_split;
-      p.lds_per_wave_otf = P->lds_split_otf;
-      e = launch_groups(P, p, st, &P->side);
+      e = launch_groups(P, p, st);
       if (e == hipSuccess) e = hipEventRecord(P->ovl.spot_done[k & 1], st);
     }
     // the last projection is joined by the wait before the last spot launch
@@ -1409,7 +1386,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       p.proj_blocks = P->proj_all.per_real * P->batch;
       p.phase_out = buf[(k + 1) & 1];
     }
-    e = launch_groups(P, p, st, &P->side);
+    e = launch_groups(P, p, st);
   }
   return e;
 }
@@ -1442,7 +1419,7 @@ int wfs_spots(wfs_plan_t P, const float* phase, int64_t step, uint64_t seed, flo
   FwdParams p = call_params(P, nullptr, step, seed, slopes, aux);
   p.phase_in = phase;
   p.otf_from_phase = 1;
-  hipError_t e = launch_groups(P, p, (hipStream_t)stream, &P->side);
+  hipError_t e = launch_groups(P, p, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "wfs_spots: launch");
   return WFS_OK;
 }
@@ -1944,8 +1921,8 @@ struct CalibCells {
 // can stage it, each actuator is an element of at most one layer, a zero-boundary grid (a
 // periodic layer's element can reach the pupil in several images), and the pokes reach fewer
 // subapertures than there are.  Measured (192 actuators of the three mirrors, 55,608 slopes,
-// batch 128): the dense batch 24.8 ms, the reached subapertures 2.27 ms (0.12 ms of it the
-// lag-domain sensors).
+// batch 128): the dense batch 24.8 ms, the reached subapertures 0.47 ms (0.12 ms of it the
+// lag-domain sensors' launch, 3 x 0.09 ms the FFT-path chunks beside it).
 static bool calib_sparse(wfs_plan_t P, int64_t act_offset, int32_t n_act, CalibCells* out) {
   if (!P->foot_ok || !(P->foot || (P->split && P->d_phase))) return false;
   for (const DevSensor& S : P->hsen)
@@ -2010,7 +1987,6 @@ static hipError_t calibrate_sparse(wfs_plan_t P, const float* layers, int64_t ac
     a.phase_in = P->d_phase;
     a.aux = nullptr;
     set_proj(a, P->proj_fft);
-    a.lds_per_wave = P->lds_split;
     const int32_t h = P->batch / 2;
     for (int32_t j0 = 0; j0 < n_act && e == hipSuccess; j0 += h) {
       CalibParams c = q;
@@ -2018,7 +1994,7 @@ static hipError_t calibrate_sparse(wfs_plan_t P, const float* layers, int64_t ac
       c.n_act = std::min(h, n_act - j0);
       c.im = im + (int64_t)j0 * ld_im;
       a.batch = 2 * c.n_act;
-      e = calib_fft(a, c, P->d_phase, P->proj_lds_fft, fs);
+      e = calib_fft(a, P->fft_tab, c, P->d_phase, P->proj_lds_fft, fs);
     }
     if (e != hipSuccess) return e;
   }
@@ -2087,7 +2063,6 @@ int wfs_calibrate(wfs_plan_t P, const float* base, int64_t act_offset, int32_t n
     FwdParams p = call_params(P, base ? base : wl, step, seed, ws, wa);
     p.batch = 1;
     p.otf_blocks = P->groups.empty() ? 0 : blocks_of(p.otf, 1);
-    p.fft_blocks = blocks_of(p.fft, 1);
     if ((e = launch_fwd_modes(P, p, st)) != hipSuccess)
       return hip_fail(e, "wfs_calibrate: reference forward");
     if (ref_slopes &&

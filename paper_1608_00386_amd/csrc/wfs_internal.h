@@ -55,9 +55,8 @@ struct DevSensor {
   int32_t foot_cols_off;  // first entry of this sensor's footprint-column table
   int32_t foot_floats;    // footprint floats of one subaperture, all layers
   float ramp_y;           // the same per pixel row: 1 / (2 n_fft) - tilt_y dx / lambda
-  int32_t fft_part_off;   // FFT path with several spectrum chunks: first float of this sensor's
-                          // partial images in one realisation's part of the partial buffer
-  int32_t fft_cnt_off;    // first of this sensor's chunk counters in one realisation's part
+  int32_t fft_cnt_off;    // FFT path with several spectrum chunks, adjoint: first of this
+                          // sensor's chunk counters in one realisation's part
   int32_t fft_adj_off;    // adjoint: first float of this sensor's chunk partials (n_sub^2 per
                           // chunk) in one realisation's part of the adjoint partial buffer
   int32_t foot_ent_off;   // staged footprint: first of this sensor's stencil entries in a
@@ -152,20 +151,16 @@ struct FwdParams {
   int32_t n_valid_total;
   // schedule
   int32_t otf_blocks;       // blocks serving the lag-domain tasks
-  int32_t fft_blocks;       // blocks serving FFT tasks (one subaperture each), launched first
   int32_t xcd_remap;
-  int32_t lds_per_wave;     // bytes (lag-domain waves, or a quarter of an FFT workgroup)
-  int32_t lds_per_wave_otf; // bytes when the launch holds no FFT-path blocks
+  int32_t lds_per_wave;     // bytes
   int32_t otf_from_phase;   // lag-domain field source: 0 gather, 1 phase_in (split), 2 footprint
-  int32_t fft_inline;       // host side: FFT-path blocks in the same launch as the others
-  // FFT path: partial binned images of the spectrum chunks ([B][fft_part_per_real] floats)
-  // and per-subaperture chunk counters ([B][fft_cnt_per_real], zero between launches)
-  float* fft_part;
+  int32_t fft_inline;       // host side: FFT-path launch on the caller's stream, not beside it
+  // FFT path, adjoint: per-subaperture chunk counters ([B][fft_cnt_per_real], zero between
+  // launches)
   int32_t* fft_cnt;
-  int64_t fft_part_per_real;
   int32_t fft_cnt_per_real;
   TaskTable otf;
-  TaskTable fft;
+  TaskTable fft;            // adjoint: one task per spectrum chunk
   // projection blocks of one realisation: (first pupil row | column strip << 16, sensor)
   const int2* proj_desc;
   int32_t proj_per_real;
@@ -188,8 +183,15 @@ struct FwdParams {
   int32_t foot_ent_per_frame;
 };
 
-// A plan-owned second stream with fork/join events: a launch that holds FFT-path blocks runs
-// them there, concurrently with the lag-domain blocks on the caller's stream.
+// FFT-path sensors of a plan by the number of spectrum chunks per axis (Q = 1, 2, 4): one task
+// per subaperture.
+struct FftTables {
+  TaskTable t[3];
+  int32_t any;
+};
+
+// A plan-owned second stream with fork/join events: the FFT-path subapertures run there,
+// concurrently with the lag-domain launch on the caller's stream.
 struct SideStream {
   hipStream_t stream = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
