@@ -7,6 +7,13 @@
 //   U[k]   = c T[k] ghat[k],  ghat[k] = sum_q g_B[q] e^{2 pi i k.q / n_pix}   (Hermitian in k)
 //   dL     = Re sum_k U[k] dA[k],  dE[m] = i E[m] dpsi[m]
 //   =>  g_psi[p] = -2 Im(E[p] V[p]),   V[p] = sum_{m'} U[m' - p] conj(E[m'])
+// g_B is a plane in q, so ghat vanishes off the axes k_x = 0 and k_y = 0 modulo n_pix, and
+// with S1[K] = sum_q q e^{2 pi i K q / n_pix} = n_pix / (e^{2 pi i K / n_pix} - 1):
+//   ghat[0] = -n_pix^2 (g_x c_x + g_y c_y) / sum B,  ghat[K_x] = n_pix g_x S1[K_x] / sum B,
+//   ghat[K_y] = n_pix g_y S1[K_y] / sum B.
+// Only the lags with dy or dx a multiple of n_pix take part (n_sub = 10, 8 x 8 pixels: 105 of
+// 361, and about 30 of the 100 field pixels per V[p]).  Bound by vector issue: the adjoint of
+// six 80 x 80 LGS without its gather took 107 us with every lag in U and V, 42 us so.
 // and the layer gradient is the transpose of the bilinear projection, kappa w_l times the
 // stencil weights (subaperture fields recomputed).  Two ways to form it:
 //   gather (default): g_psi (kappa applied) goes to a phase-layout buffer, then one thread per
@@ -21,48 +28,31 @@
 
 namespace wfs {
 
-struct AdjLds {
-  int u_off, gz_off, gh_off, gb_off, total;
-};
-
-// Row pitch (float2) of the adjoint's lag array U: at least 2 n_sub - 1 and congruent to n_sub
-// modulo 16, so that lane q = r n_sub + c of the correlation loop, reading U at offset
-// -(pitch r + c), falls on bank pair q mod 16: every half-wave meets each pair twice, the
-// fewest a 64-bit read can (a pitch of 2 n_sub - 1 put up to four lanes on one pair).
-__host__ __device__ constexpr int adj_u_pitch(int ns) {
-  return 2 * ns - 1 + (((1 - ns) % 16) + 16) % 16;
+// Lag classes of one axis: the multiples of n_pix among the lags -(ns-1) .. ns-1.
+__host__ __device__ inline int adj_classes(int ns, int n_pix) {
+  return 1 + 2 * ((ns - 1) / n_pix);
 }
 
-// Per-wave LDS of the adjoint: the forward layout, then the backward arrays U, GZ, GH, gB.  Once
-// the spot (or only the field) is formed, only E and the sensor tables of the forward layout
-// are read again, so in the gather form (no stencil taps) the backward arrays go into the dead
-// regions between E and the tables when they fit (n_sub = 10, 8 x 8 pixels: 7.3 KB per wave
-// instead of 12.7 KB, 5 four-wave blocks a CU instead of 3); the atomic form keeps its taps in
-// the forward union and places the backward arrays after the forward layout.
+struct AdjLds {
+  int ur_off, uc_off, g_off, total;
+};
+
+// Per-wave LDS of the adjoint: the forward layout and U on the lag classes: UR [classes][2 ns -
+// 1] (dy a multiple of n_pix, every dx) and UC (dx a multiple, every dy; zero where dy is one
+// too), then ghat along x and y.  Once the spot (or only the field) is formed, only E and the
+// lag-phase table of the forward layout are read again, so in the gather form (no stencil
+// taps) these go into the dead union between them when they fit; the atomic form keeps its
+// taps there and places them after the forward layout.
 __host__ __device__ inline AdjLds adj_lds_layout(int ns, int n_layers, int n_pix, bool gather) {
   const OtfLds f = otf_lds_layout(ns, n_layers, n_pix);
-  const int nl = 2 * ns - 1, np2 = n_pix * n_pix;
+  const int ub = adj_classes(ns, n_pix) * (2 * ns - 1) * 8;
   AdjLds a;
-  const int ub = nl * adj_u_pitch(ns) * 8, gbb = (np2 * 4 + 7) & ~7, gzb = np2 * 8;
   const int e_end = (ns * ns * 8 + 15) & ~15;
-  if (gather && e_end + ub + gbb + 2 * gzb <= f.stab_off) {
-    a.u_off = e_end;
-    a.gb_off = a.u_off + ub;
-    a.gz_off = a.gb_off + gbb;
-    a.gh_off = a.gz_off + gzb;
-    a.total = f.total;
-    return a;
-  }
-  int o = f.total;
-  a.u_off = o;
-  o += nl * adj_u_pitch(ns) * 8;
-  a.gz_off = o;
-  o += np2 * 8;
-  a.gh_off = o;
-  o += np2 * 8;
-  a.gb_off = o;
-  o += np2 * 4;
-  a.total = (o + 15) & ~15;
+  const bool in = gather && e_end + 2 * ub + 2 * n_pix * 8 <= f.tw_off;
+  a.ur_off = in ? e_end : f.total;
+  a.uc_off = a.ur_off + ub;
+  a.g_off = a.uc_off + ub;
+  a.total = in ? f.total : (a.g_off + 2 * n_pix * 8 + 15) & ~15;
   return a;
 }
 
@@ -98,73 +88,46 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
   float* gout = ap.gpsi ? ap.gpsi + (int64_t)b * p.pupil_per_real + S.pupil_off +
                               (int64_t)sb.a * NS * S.n_pup + sb.b * NS
                         : nullptr;
-  if (!(s0 > 0.0f) || (gx == 0.0f && gy == 0.0f)) {  // wave-uniform: no gradient (the image
-    return;                                            // was cleared before the launch)
+  if (!(s0 > 0.0f) || (gx == 0.0f && gy == 0.0f)) {  // wave-uniform: no gradient
+    if (gout)
+      for (int q = lane; q < NS * NS; q += kWave) {
+        const int r = small_div<NS>(q);
+        gout[r * S.n_pup + q - r * NS] = 0.0f;
+      }
+    return;
   }
-
-  const float half = 0.5f * (float)(np - 1);
-  const float inv = 1.0f / s0;
-  float* gB = reinterpret_cast<float*>(wsm + la.gb_off);
-  for (int q = lane; q < np2; q += kWave) {
-    const int qy = fdiv(q, np, S.inv_npix), qx = q - qy * np;
-    gB[q] = (gx * ((float)qx - half - cx) + gy * ((float)qy - half - cy)) * inv;
-  }
-  wave_sync();
-  // ghat[Ky][Kx] = sum_q gB[q] W^{Kx qx + Ky qy}, separable (W = e^{2 pi i / n_pix})
-  const float2* wt = reinterpret_cast<const float2*>(wsm + lo.wtab_off);
-  float2* GZ = reinterpret_cast<float2*>(wsm + la.gz_off);  // [qy][Kx]
-  for (int t2 = lane; t2 < np2; t2 += kWave) {
-    const int qy = fdiv(t2, np, S.inv_npix), Kx = t2 - qy * np;
-    float2 z = make_float2(0.0f, 0.0f);
-    int idx = 0;
-    for (int qx = 0; qx < np; ++qx) {
-      const float g = gB[qy * np + qx];
-      const float2 w = wt[idx];
-      z.x = fmaf(g, w.x, z.x);
-      z.y = fmaf(g, w.y, z.y);
-      idx += Kx;
-      if (idx >= np) idx -= np;
-    }
-    GZ[t2] = z;
-  }
-  wave_sync();
-  float2* GH = reinterpret_cast<float2*>(wsm + la.gh_off);  // [Ky][Kx]
-  for (int t2 = lane; t2 < np2; t2 += kWave) {
-    const int Ky = fdiv(t2, np, S.inv_npix), Kx = t2 - Ky * np;
-    float2 h = make_float2(0.0f, 0.0f);
-    int idx = 0;
-    for (int qy = 0; qy < np; ++qy) {
-      const float2 z = GZ[qy * np + Kx];
-      const float2 w = wt[idx];
-      h.x = fmaf(z.x, w.x, fmaf(-z.y, w.y, h.x));
-      h.y = fmaf(z.x, w.y, fmaf(z.y, w.x, h.y));
-      idx += Ky;
-      if (idx >= np) idx -= np;
-    }
-    GH[t2] = h;
-  }
-  wave_sync();
-  // U[k] = c Kel(k) s(kx) s(ky) ghat[k mod n_pix] on all (2 NS - 1)^2 lags
   constexpr int NL = 2 * NS - 1;
-  constexpr int UP = adj_u_pitch(NS);
+  const int ncl = adj_classes(NS, np), hcl = ncl >> 1;
+  const float inv = 1.0f / s0;
+  float2* GX = reinterpret_cast<float2*>(wsm + la.g_off);  // ghat along x, then along y
+  float2* GY = GX + np;
+  for (int K = lane; K < np; K += kWave) {
+    const float2 s1 = p.wtab[S.wtab_off + np + K];  // n_pix S1[K], 0 at K = 0
+    const float fx = gx * inv, fy = gy * inv;
+    float2 hx = make_float2(fx * s1.x, fx * s1.y);
+    if (K == 0) hx.x = -(float)np2 * (fx * cx + fy * cy);
+    GX[K] = hx;
+    GY[K] = make_float2(fy * s1.x, fy * s1.y);
+  }
+  wave_sync();
+  // U[k] = c Kel(k) s(kx) s(ky) ghat[k mod n_pix] on the lag classes
   const NaEntry el = na_entry(p, step);
-  float2* U = reinterpret_cast<float2*>(wsm + la.u_off);
+  float2* UR = reinterpret_cast<float2*>(wsm + la.ur_off);
+  float2* UC = reinterpret_cast<float2*>(wsm + la.uc_off);
   const float2* stab = reinterpret_cast<const float2*>(wsm + lo.stab_off);
-  for (int t2 = lane; t2 < NL * NL; t2 += kWave) {
-    const int iy = t2 / NL, ix = t2 - iy * NL;
-    const int dy = iy - (NS - 1), dx = ix - (NS - 1);
-    // lags -> bins modulo n_pix (|lag| < NS, so one shift by a multiple of n_pix is enough)
-    const int dyp = dy + np * NS, dxp = dx + np * NS;
-    const int Ky = dyp - np * fdiv(dyp, np, S.inv_npix);
-    const int Kx = dxp - np * fdiv(dxp, np, S.inv_npix);
-    const float2 g = GH[Ky * np + Kx];
-    const float2 sx = stab[ix], sy = stab[iy];
-    const float proj = fmaf((float)dx, sb.ex, (float)dy * sb.ey);
-    const float2 k = elong_tf(sb, el, proj, S.flux_c);
-    const float sr = sx.x * sy.x - sx.y * sy.y, si = sx.x * sy.y + sx.y * sy.x;
-    const float tr = sr * k.x - si * k.y;
-    const float ti = sr * k.y + si * k.x;
-    U[iy * UP + ix] = make_float2(tr * g.x - ti * g.y, tr * g.y + ti * g.x);
+  auto lag_u = [&](int dy, int dx, float2 g) {
+    const float2 k = elong_tf(sb, el, fmaf((float)dx, sb.ex, (float)dy * sb.ey), S.flux_c);
+    return cmul2(cmul2(cmul2(stab[dx + NS - 1], stab[dy + NS - 1]), k), g);
+  };
+  for (int t2 = lane; t2 < 2 * ncl * NL; t2 += kWave) {
+    const bool col = t2 >= ncl * NL;
+    const int u = col ? t2 - ncl * NL : t2;
+    const int cls = small_div<NL>(u), i = u - cls * NL;
+    const int d = (cls - hcl) * np, e = i - (NS - 1);  // the class's lag and the other axis'
+    const int ep = e + np * NS;  // lags -> bins modulo n_pix
+    const int K = ep - np * fdiv(ep, np, S.inv_npix);
+    // UC leaves the lags of both classes to UR (GY[0] = 0)
+    UR[t2] = lag_u(col ? e : d, col ? d : e, col ? GY[K] : GX[K]);
   }
   // taps again (the forward scratch region is free now); the gather mode needs none
   const int nlay = p.n_layers;
@@ -180,24 +143,56 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
   wave_sync();
   const float2* E = reinterpret_cast<const float2*>(wsm + lo.e_off);
   float* gl = ap.grad_layers + (int64_t)b * p.layer_stride;
-  for (int q = lane; q < NS * NS; q += kWave) {
-    const int r = q / NS, c = q - r * NS;
-    const float2 e = E[q];
-    if (e.x == 0.0f && e.y == 0.0f) continue;  // dark pixel
-    float2 V = make_float2(0.0f, 0.0f);
-#pragma unroll 2
-    for (int r2 = 0; r2 < NS; ++r2) {
-      const float2* urow = U + (r2 - r + NS - 1) * UP + (NS - 1 - c);
+  // lane (column c, row group): pixels (rg + slot RG, c); the field pixels of the row and
+  // column classes of a pixel, n_pix apart from its own row (z: r2 = r mod n_pix + z n_pix)
+  constexpr int RG = kWave / NS < NS ? kWave / NS : NS, SLOTS = (NS + RG - 1) / RG;
+  const int rg = small_div<NS>(lane), c = lane - rg * NS;
+  const int nz = fdiv(NS + np - 1, np, S.inv_npix);
+  const int c0 = c - np * fdiv(c, np, S.inv_npix);
+  int rr[SLOTS];
+  float2 V[SLOTS];
 #pragma unroll
-      for (int c2 = 0; c2 < NS; ++c2) {
-        const float2 u = urow[c2];
-        const float2 f = E[r2 * NS + c2];
-        // u * conj(f)
-        V.x = fmaf(u.x, f.x, fmaf(u.y, f.y, V.x));
-        V.y = fmaf(u.y, f.x, fmaf(-u.x, f.y, V.y));
+  for (int k = 0; k < SLOTS; ++k) {
+    rr[k] = min(rg + k * RG, NS - 1);
+    V[k] = make_float2(0.0f, 0.0f);
+  }
+  // u conj(f)
+  auto corr = [](float2 u, float2 f, float2 v) {
+    return make_float2(fmaf(u.x, f.x, fmaf(u.y, f.y, v.x)),
+                       fmaf(u.y, f.x, fmaf(-u.x, f.y, v.y)));
+  };
+  for (int z = 0; z < nz; ++z) {
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      const int r0 = rr[k] - np * fdiv(rr[k], np, S.inv_npix), r2 = r0 + z * np;
+      if (r2 < NS) {
+        const int cls = fdiv(r2 - rr[k] + np * NS, np, S.inv_npix) - NS + hcl;
+        const float2* u = UR + cls * NL + (NS - 1 - c);
+#pragma unroll
+        for (int c2 = 0; c2 < NS; ++c2) V[k] = corr(u[c2], E[r2 * NS + c2], V[k]);
       }
     }
-    const float gpsi = -2.0f * (e.x * V.y + e.y * V.x) * S.kappa;
+    const int c2 = c0 + z * np;
+    if (c2 < NS) {
+      const int cls = fdiv(c2 - c + np * NS, np, S.inv_npix) - NS + hcl;
+      float2 f[NS];
+#pragma unroll
+      for (int r2 = 0; r2 < NS; ++r2) f[r2] = E[r2 * NS + c2];
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) {
+        const float2* u = UC + cls * NL + (NS - 1 - rr[k]);
+#pragma unroll
+        for (int r2 = 0; r2 < NS; ++r2) V[k] = corr(u[r2], f[r2], V[k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < SLOTS; ++k) {
+    const int r = rg + k * RG;
+    if (rg >= RG || r >= NS) continue;
+    const float2 e = E[r * NS + c];
+    if (!gout && e.x == 0.0f && e.y == 0.0f) continue;  // dark pixel
+    const float gpsi = -2.0f * (e.x * V[k].y + e.y * V[k].x) * S.kappa;
     if (gout) {
       gout[r * S.n_pup + c] = gpsi;
       continue;
@@ -657,27 +652,25 @@ __global__ __launch_bounds__(kBlock) void zero_kernel(float* x, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) x[i] = 0.0f;
 }
 
+hipError_t launch_zero(float* x, int64_t n, hipStream_t st) {
+  const int zb = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 8192);
+  hipLaunchKernelGGL(zero_kernel, dim3(zb > 0 ? zb : 1), dim3(kBlock), 0, st, x, n);
+  return hipGetLastError();
+}
+
 template <int NS>
 static hipError_t launch_adj(AdjParams a, bool clear_grad, bool clear, hipStream_t st) {
-  // atomic mode accumulates into the gradient; gather mode into the phase-gradient images
-  // (cleared by the first of the launches that add into them)
+  // atomic mode accumulates into the gradient (gather mode writes every pixel of a valid
+  // subaperture of its images; the others stay zero from their allocation)
   hipError_t e = hipSuccess;
-  if (clear) {
-    float* z = a.gpsi ? a.gpsi : a.grad_layers;
-    const int64_t n = a.gpsi ? a.f.pupil_per_real * a.f.batch : a.f.layer_stride * a.f.batch;
-    const int zb = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 8192);
-    hipLaunchKernelGGL(zero_kernel, dim3(zb > 0 ? zb : 1), dim3(kBlock), 0, st, z, n);
-    e = hipGetLastError();
+  if (clear && !a.gpsi) {
+    e = launch_zero(a.grad_layers, a.f.layer_stride * a.f.batch, st);
     if (e != hipSuccess) return e;
   }
   // the gather writes every grid pixel; the rest of the gradient buffer (gaps between the
   // grids inside the stride) is cleared only when there is such a gap
   if (clear && a.gpsi && clear_grad) {
-    const int64_t ng = a.f.layer_stride * a.f.batch;
-    const int zg = (int)std::min<int64_t>((ng + kBlock - 1) / kBlock, 8192);
-    hipLaunchKernelGGL(zero_kernel, dim3(zg > 0 ? zg : 1), dim3(kBlock), 0, st, a.grad_layers,
-                       ng);
-    e = hipGetLastError();
+    e = launch_zero(a.grad_layers, a.f.layer_stride * a.f.batch, st);
     if (e != hipSuccess) return e;
   }
   const int64_t tasks = (int64_t)a.f.otf.per_real * a.f.batch;
@@ -695,6 +688,14 @@ static hipError_t launch_adj(AdjParams a, bool clear_grad, bool clear, hipStream
 
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather) {
   return adj_lds_layout(ns, n_layers, n_pix, gather).total;
+}
+
+// Whether wfs_adjoint takes lag-domain sensors of this size: images whose forward layout, a
+// whole lag array and three image-sized arrays fit 64 KiB per workgroup.
+bool adj_takes(int ns, int n_layers, int n_pix) {
+  const int nl = 2 * ns - 1, pitch = nl + (((1 - ns) % 16) + 16) % 16;
+  return (otf_lds_layout(ns, n_layers, n_pix).total + nl * pitch * 8 + 20 * n_pix * n_pix) *
+             kWavesPerBlock <= 65536;
 }
 
 hipError_t launch_adjoint_gather(const FwdParams& f, const float* gpsi, float* grad,

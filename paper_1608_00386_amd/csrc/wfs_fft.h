@@ -430,13 +430,19 @@ __device__ void fft_adjoint_chunk_m(const AdjParams& ap, const DevSensor& S, int
   const int v = u / Q2, c = u - v * Q2;
   const int k1y = c / Q, k1x = c - k1y * Q;
   // forward outputs and slope gradients of the subaperture (wave-uniform; all its chunks
-  // take the same decision, so a subaperture without gradient writes nothing)
+  // take the same decision; chunk 0 writes the zeros of a subaperture without gradient)
   const int64_t so = (int64_t)b * p.n_slopes + S.slope_off + v;
   const float gx = ap.grad_slopes[so], gy = ap.grad_slopes[so + S.n_valid];
   const float cx = ap.fwd_slopes[so], cy = ap.fwd_slopes[so + S.n_valid];
   const float s0 = ap.fwd_aux[(int64_t)b * p.n_valid_total + S.aux_off + v];
-  if (!(s0 > 0.0f) || (gx == 0.0f && gy == 0.0f)) return;
   const DevSubap sb = cload(p.sub, S.valid_off + v);
+  float* gout = ap.gpsi + (int64_t)b * p.pupil_per_real + S.pupil_off +
+                (int64_t)sb.a * n * S.n_pup + sb.b * n;
+  if (!(s0 > 0.0f) || (gx == 0.0f && gy == 0.0f)) {
+    if (c == 0)
+      for (int q = lane; q < n * n; q += kWave) gout[(q / n) * S.n_pup + q % n] = 0.0f;
+    return;
+  }
   const int nx1 = (n + M - 1) / M;
   float2* X = reinterpret_cast<float2*>(wsm);              // [M][M + 1]
   float* gB = reinterpret_cast<float*>(wsm + M * (M + 1) * 8);  // [np][np]
@@ -531,8 +537,6 @@ __device__ void fft_adjoint_chunk_m(const AdjParams& ap, const DevSensor& S, int
   wave_sync();
   // 4. this chunk's share of g_psi on the field pixels m = (y2 + M y1, x2 + M x1)
   const float c2k = 2.0f * S.flux_c * S.kappa;
-  float* gout = ap.gpsi + (int64_t)b * p.pupil_per_real + S.pupil_off +
-                (int64_t)sb.a * n * S.n_pup + sb.b * n;
   float* part = Q == 1 ? nullptr
                        : ap.fft_adj_part + (int64_t)b * ap.fft_adj_per_real + S.fft_adj_off +
                              ((int64_t)v * Q2 + c) * (n * n);

@@ -28,6 +28,7 @@ int project_max_groups();
 int project_strip();
 int project_rows();
 hipError_t launch_step(int64_t* step_dev, int64_t value, int add, hipStream_t st);
+hipError_t launch_zero(float* x, int64_t n, hipStream_t st);
 hipError_t launch_adjoint(const AdjParams& a, int ns, bool clear_grad, bool clear,
                           hipStream_t st);
 hipError_t launch_adjoint_gather(const FwdParams& f, const float* gpsi, float* grad,
@@ -40,6 +41,7 @@ int adj_tab_rows();
 int fft_adj_wave_lds_bytes(int n_fft, int n_pix);
 hipError_t launch_adjoint_fft(const AdjParams& a, int lds_per_wave, hipStream_t st);
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather);
+bool adj_takes(int ns, int n_layers, int n_pix);
 hipError_t recon_work_floats(const float* R, int M, int N, const float* S, int B,
                              int64_t* floats);
 hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, bool* capturing);
@@ -569,6 +571,13 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
       const double a = 2.0 * M_PI * t / d.n_pix;
       wtab.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
     }
+    // then the adjoint's n_pix sum_q q e^{2 pi i K q / n_pix} = n_pix^2 / (e^{2 pi i K / n_pix}
+    // - 1), 0 at K = 0
+    for (int t = 0; t < d.n_pix; ++t) {
+      const double n2 = (double)d.n_pix * d.n_pix, h = M_PI * t / d.n_pix;
+      wtab.push_back(t ? make_float2((float)(-0.5 * n2), (float)(-0.5 * n2 * std::cos(h) / std::sin(h)))
+                       : make_float2(0.0f, 0.0f));
+    }
     // cone + frozen-flow affine maps: X = s x + theta h - v t, u = X / pitch + n/2 - 1/2
     const double H = S.src_alt_m;
     for (int l = 0; l < n_layers; ++l) {
@@ -971,10 +980,10 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
     // the adjoint's form (gather unless asked for atomics), as wfs_adjoint decides it
     const bool adj_gather =
         !(flags & WFS_FLAG_ADJOINT_ATOMIC) && P->pupil_per_real < (1LL << 30);
-    // (each wave lays out its own sensor's image size: take the largest over the sizes)
+    // (each wave lays out its own sensor's image size: the largest of the group's)
     int adj_max = 0;
-    for (int np = 1; np <= G.max_npix; ++np)
-      adj_max = std::max(adj_max, adj_lds_bytes(G.ns, n_layers, np, adj_gather));
+    for (int s : G.ids)
+      adj_max = std::max(adj_max, adj_lds_bytes(G.ns, n_layers, ds[s].n_pix, adj_gather));
     G.lds_adj = r16(adj_max);
     if (G.lds_fused * kWavesPerBlock > 65536) {
       (void)hipFree(P->d_blob);
@@ -983,7 +992,8 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
                   G.lds_fused * kWavesPerBlock);
     }
     foot_ok = foot_ok && G.lds_foot * kWavesPerBlock <= 65536;
-    adj_ok = adj_ok && G.lds_adj * kWavesPerBlock <= 65536;
+    adj_ok = adj_ok && adj_takes(G.ns, n_layers, G.max_npix) &&
+             G.lds_adj * kWavesPerBlock <= 65536;
   }
   P->lds_foot = otf_ns ? P->groups[0].lds_foot : 0;
   P->foot_ok = otf_ns && foot_ok && foot_ent > 0 && foot_ent < (1LL << 31) / 64;
@@ -1607,6 +1617,13 @@ int wfs_adjoint(wfs_plan_t P, const float* layers, const float* grad_slopes,
     hipError_t ea = hipMalloc((void**)&P->d_gimg,
                               sizeof(float) * (size_t)P->pupil_per_real * P->batch);
     if (ea != hipSuccess) {
+      P->d_gimg = nullptr;
+      return hip_fail(ea, "wfs_adjoint: phase-gradient images");
+    }
+    // pixels outside the valid subapertures are never written: zero from here on
+    ea = launch_zero(P->d_gimg, P->pupil_per_real * P->batch, (hipStream_t)stream);
+    if (ea != hipSuccess) {
+      (void)hipFree(P->d_gimg);
       P->d_gimg = nullptr;
       return hip_fail(ea, "wfs_adjoint: phase-gradient images");
     }

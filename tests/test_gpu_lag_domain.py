@@ -49,3 +49,32 @@ def test_spots_of_every_subaperture_size_match_the_oracle(n_sub, N, b, noise, el
                                    err_msg=mode)
     assert np.array_equal(got["split"][0], got["footprint"][0])
     assert np.array_equal(got["split"][1], got["footprint"][1])
+
+
+# images from 2 pixels (every lag in a class) to more pixels than the subaperture has (the
+# axes through zero lag only), classes that leave and do not leave a remainder
+ADJ = [(2, 4, 2), (3, 6, 1), (4, 8, 4), (5, 10, 2), (6, 12, 6), (7, 14, 7), (8, 16, 4),
+       (8, 24, 1), (9, 18, 3), (10, 32, 4), (10, 20, 10), (11, 22, 2), (12, 24, 12), (12, 24, 3)]
+
+
+@pytest.mark.parametrize("n_sub,N,b", ADJ)
+@pytest.mark.parametrize("atomic", [False, True])
+def test_adjoint_of_every_image_size_matches_the_oracle(n_sub, N, b, atomic):
+    import torch
+    import paper_1608_00386_amd as W
+    from wfs_cases import layers_for
+    cfg = lgs_case(5, n_sub, N, b, layers=2, n=96, pitch=0.25, n_sensors=2)
+    x = layers_for(cfg)
+    g = np.random.default_rng(3).standard_normal((1, 2 * sum(
+        len(oracle.pupil_geometry(s)["valid"]) for s in cfg["sensors"]))).astype(np.float32)
+    g[0, 1] = g[0, 1 + g.shape[1] // 4] = 0.0  # a subaperture without gradient
+    plan = W.Plan(cfg, flags=W.WFS_FLAG_ADJOINT_ATOMIC if atomic else 0)
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    ref = oracle.adjoint(x.astype(np.float64), cfg, 3, g.astype(np.float64))
+    s, a = plan.forward(xt, step=3)
+    for fwd in ({}, dict(fwd_slopes=s, fwd_aux=a)):
+        got = plan.adjoint(xt, gt, step=3, **fwd).cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
+        assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max()
+    zero = plan.adjoint(xt, torch.zeros_like(gt), step=3)  # nothing left from the calls before
+    assert not zero.any()
