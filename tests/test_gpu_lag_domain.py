@@ -54,7 +54,7 @@ def test_spots_of_every_subaperture_size_match_the_oracle(n_sub, N, b, noise, el
 # images from 2 pixels (every lag in a class) to more pixels than the subaperture has (the
 # axes through zero lag only), classes that leave and do not leave a remainder
 ADJ = [(2, 4, 2), (3, 6, 1), (4, 8, 4), (5, 10, 2), (6, 12, 6), (7, 14, 7), (8, 16, 4),
-       (8, 24, 1), (9, 18, 3), (10, 32, 4), (10, 20, 10), (11, 22, 2), (12, 24, 12), (12, 24, 3)]
+       (8, 24, 2), (9, 18, 3), (10, 32, 4), (10, 20, 10), (11, 22, 2), (12, 24, 12), (12, 24, 3)]
 
 
 @pytest.mark.parametrize("n_sub,N,b", ADJ)
