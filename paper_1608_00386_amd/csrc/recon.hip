@@ -3,23 +3,25 @@
 // coefficients added to the mirror).  R is [M][N] row-major FP32 and is streamed from HBM once
 // per call; that stream bounds the operation (4 flop per byte of R at B = 8).
 //
-//   B == 1, or unaligned operands : split-K streaming GEMV on the vector ALUs
-//   2 <= B <= 8, 16-byte aligned   : the same streaming order with every realisation at once
-//   (N % 4 == 0)                     (vector ALUs; R read once in 1 KB bursts per row, the
-//                                    slopes staged in LDS per workgroup)
-//   B > 8, aligned                 : split-K GEMM on the FP32 matrix cores
-//                                    (v_mfma_f32_16x16x4f32, one 16-row x 16-realisation tile
-//                                    per MFMA, 2 row tiles per wavefront)
+//   B == 1      : split-K streaming GEMV on the vector ALUs
+//   2 <= B <= 8 : the same streaming order with every realisation at once (vector ALUs; R read
+//                 once in 1 KB bursts per row, the slopes staged in LDS per workgroup)
+//   B > 8       : split-K GEMM on the FP32 matrix cores, up to 32 realisations a pass, R and
+//                 the slopes staged in LDS
 // Both write per-split partial sums to a workspace; a second kernel adds the splits in a fixed
-// order and applies alpha/beta, so results are deterministic.
+// order and applies alpha/beta, so results are deterministic.  R and S need no more than their
+// natural 4-byte alignment: 16-byte loads of any row (N need not be a multiple of 4) take the
+// hardware's unaligned access, the last 1-3 columns of a row element by element.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/wfs.h"
+#include "wfs_common.h"
 
 namespace wfs {
 
@@ -29,17 +31,34 @@ constexpr int kBatchMax = 8;  // realisations of the small-batch kernel
 constexpr bool kBatchPF = true;  // small-batch kernel: next slice's rows of R in flight
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
 
-// 16-byte streaming load of R (read once per call: non-temporal)
+// 16-byte streaming load of R (read once per call: non-temporal), 4-byte aligned
 __device__ __forceinline__ float4 ldnt4(const float* p) {
-  const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
+  const v4fu v = __builtin_nontemporal_load(reinterpret_cast<const v4fu*>(p));
   return make_float4(v.x, v.y, v.z, v.w);
+}
+
+__device__ __forceinline__ float4 ld4(const float* p) {
+  const v4fu v = *reinterpret_cast<const v4fu*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Columns k .. k + 3 of a row below k1, zero past it.
+template <bool NT>
+__device__ __forceinline__ float4 ld4_below(const float* row, int k, int k1) {
+  if (k + 4 <= k1) return NT ? ldnt4(row + k) : ld4(row + k);
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (k < k1) v.x = row[k];
+  if (k + 1 < k1) v.y = row[k + 1];
+  if (k + 2 < k1) v.z = row[k + 2];
+  return v;
 }
 
 // ---------------------------------------------------------------------------------------
 // GEMV / generic: wave per (RW rows, split); lanes stride over k.
 // ---------------------------------------------------------------------------------------
-template <int RW, bool VEC>
+template <int RW>
 __global__ __launch_bounds__(kRB) void recon_valu_kernel(const float* __restrict__ R, int M,
                                                          int N, const float* __restrict__ S,
                                                          int b, int chunk, int splits,
@@ -54,43 +73,37 @@ __global__ __launch_bounds__(kRB) void recon_valu_kernel(const float* __restrict
   float acc[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) acc[r] = 0.0f;
-  if (VEC) {
-    // k0 and N are multiples of 4; rows 16-byte aligned; two steps of loads in flight
-    int k = k0 + 4 * lane;
-    for (; k + 4 * 64 < k1; k += 2 * 4 * 64) {
-      const float4 s0 = *reinterpret_cast<const float4*>(s + k);
-      const float4 s1 = *reinterpret_cast<const float4*>(s + k + 256);
-      float4 r0[RW], r1[RW];
+  // whole float4s of the chunk; two steps of loads in flight
+  const int kv = k0 + ((k1 - k0) & ~3);
+  int k = k0 + 4 * lane;
+  for (; k + 4 * 64 < kv; k += 2 * 4 * 64) {
+    const float4 s0 = ld4(s + k), s1 = ld4(s + k + 256);
+    float4 r0[RW], r1[RW];
 #pragma unroll
-      for (int r = 0; r < RW; ++r) {
-        const int row = min(row0 + r, M - 1);
-        r0[r] = ldnt4(R + (int64_t)row * N + k);
-        r1[r] = ldnt4(R + (int64_t)row * N + k + 256);
-      }
-#pragma unroll
-      for (int r = 0; r < RW; ++r) {
-        acc[r] = fmaf(r0[r].x, s0.x, fmaf(r0[r].y, s0.y, fmaf(r0[r].z, s0.z, fmaf(r0[r].w, s0.w, acc[r]))));
-        acc[r] = fmaf(r1[r].x, s1.x, fmaf(r1[r].y, s1.y, fmaf(r1[r].z, s1.z, fmaf(r1[r].w, s1.w, acc[r]))));
-      }
+    for (int r = 0; r < RW; ++r) {
+      const int row = min(row0 + r, M - 1);
+      r0[r] = ldnt4(R + (int64_t)row * N + k);
+      r1[r] = ldnt4(R + (int64_t)row * N + k + 256);
     }
-    for (; k < k1; k += 4 * 64) {
-      const float4 sv = *reinterpret_cast<const float4*>(s + k);
 #pragma unroll
-      for (int r = 0; r < RW; ++r) {
-        const int row = min(row0 + r, M - 1);
-        const float4 rv = ldnt4(R + (int64_t)row * N + k);
-        acc[r] = fmaf(rv.x, sv.x, fmaf(rv.y, sv.y, fmaf(rv.z, sv.z, fmaf(rv.w, sv.w, acc[r]))));
-      }
+    for (int r = 0; r < RW; ++r) {
+      acc[r] = fmaf(r0[r].x, s0.x, fmaf(r0[r].y, s0.y, fmaf(r0[r].z, s0.z, fmaf(r0[r].w, s0.w, acc[r]))));
+      acc[r] = fmaf(r1[r].x, s1.x, fmaf(r1[r].y, s1.y, fmaf(r1[r].z, s1.z, fmaf(r1[r].w, s1.w, acc[r]))));
     }
-  } else {
-    for (int k = k0 + lane; k < k1; k += 64) {
-      const float sv = s[k];
+  }
+  for (; k < kv; k += 4 * 64) {
+    const float4 sv = ld4(s + k);
 #pragma unroll
-      for (int r = 0; r < RW; ++r) {
-        const int row = min(row0 + r, M - 1);
-        acc[r] = fmaf(R[(int64_t)row * N + k], sv, acc[r]);
-      }
+    for (int r = 0; r < RW; ++r) {
+      const int row = min(row0 + r, M - 1);
+      const float4 rv = ldnt4(R + (int64_t)row * N + k);
+      acc[r] = fmaf(rv.x, sv.x, fmaf(rv.y, sv.y, fmaf(rv.z, sv.z, fmaf(rv.w, sv.w, acc[r]))));
     }
+  }
+  if (kv + lane < k1) {  // the last 1-3 columns
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+      acc[r] = fmaf(R[(int64_t)min(row0 + r, M - 1) * N + kv + lane], s[kv + lane], acc[r]);
   }
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
@@ -107,7 +120,7 @@ __global__ __launch_bounds__(kRB) void recon_valu_kernel(const float* __restrict
 }
 
 // ---------------------------------------------------------------------------------------
-// Small batch (2 <= B <= 8, aligned), slopes staged in LDS: workgroup = one split (columns
+// Small batch (2 <= B <= 8), slopes staged in LDS: workgroup = one split (columns
 // [k0, k1)) x 4 row groups of 8 rows, one per wave.  The split's columns go by in slices of
 // 256: the workgroup stages the slice of every realisation's slopes in LDS (double-buffered,
 // the next slice's global loads in flight while this one is used; one barrier a slice), and
@@ -135,13 +148,16 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
 #pragma unroll
   for (int r = 0; r < RW; ++r) rrow[r] = R + (int64_t)min(row0 + r, M - 1) * N;
   // slope slice loads: thread t stages float4 j = t & 63 of realisations t / 64 and 4 + t / 64
-  auto load_s = [&](int s, float4 (&v)[2]) {
+  auto load_s = [&](int s, auto whole, float4 (&v)[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int b = (threadIdx.x >> 6) + 4 * h, k = k0 + 256 * s + 4 * (threadIdx.x & 63);
-      v[h] = (b < B && b < BB && k < k1)
-                 ? *reinterpret_cast<const float4*>(S + (int64_t)b * N + k)
-                 : make_float4(0.f, 0.f, 0.f, 0.f);
+      if (b >= B || b >= BB)
+        v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+      else if (whole)
+        v[h] = ld4(S + (int64_t)b * N + k);
+      else
+        v[h] = ld4_below<false>(S + (int64_t)b * N, k, k1);
     }
   };
   auto store_s = [&](int buf, const float4 (&v)[2]) {
@@ -151,10 +167,15 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
       if (b < BB) slab[buf][b][threadIdx.x & 63] = v[h];
     }
   };
-  auto load_r = [&](int s, float4 (&v)[RW]) {
+  auto load_r = [&](int s, auto whole, float4 (&v)[RW]) {
     const int k = k0 + 256 * s + 4 * lane;
+    if (whole) {
 #pragma unroll
-    for (int r = 0; r < RW; ++r) v[r] = k < k1 ? ldnt4(rrow[r] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int r = 0; r < RW; ++r) v[r] = ldnt4(rrow[r] + k);
+    } else {
+#pragma unroll
+      for (int r = 0; r < RW; ++r) v[r] = ld4_below<true>(rrow[r], k, k1);
+    }
   };
   float acc[RW][BB];
 #pragma unroll
@@ -162,17 +183,18 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
 #pragma unroll
     for (int b = 0; b < BB; ++b) acc[r][b] = 0.0f;
   float4 sv[2], rv[RW], rn[RW];
-  load_s(0, sv);
-  if constexpr (PF) load_r(0, rv);
+  load_s(0, std::false_type{}, sv);
+  if constexpr (PF) load_r(0, std::false_type{}, rv);
   store_s(0, sv);
   __syncthreads();
-  for (int s = 0; s < ns; ++s) {
+  // step s; the next slice's loads (a slice that may be short has a branch for each load)
+  auto step = [&](int s, auto next, auto whole) {
     const int cur = s & 1;
-    if (s + 1 < ns) load_s(s + 1, sv);
+    if (next) load_s(s + 1, whole, sv);
     if constexpr (PF) {
-      if (s + 1 < ns) load_r(s + 1, rn);
+      if (next) load_r(s + 1, whole, rn);
     } else {
-      load_r(s, rv);
+      load_r(s, std::false_type{}, rv);
     }
 #pragma unroll
     for (int b = 0; b < BB; ++b) {
@@ -182,13 +204,18 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
         acc[r][b] = fmaf(rv[r].x, x.x, fmaf(rv[r].y, x.y,
                     fmaf(rv[r].z, x.z, fmaf(rv[r].w, x.w, acc[r][b]))));
     }
-    if (s + 1 < ns) store_s(cur ^ 1, sv);
-    __syncthreads();
-    if constexpr (PF) {
+    if (next) {
+      store_s(cur ^ 1, sv);
+      __syncthreads();
+      if constexpr (PF) {
 #pragma unroll
-      for (int r = 0; r < RW; ++r) rv[r] = rn[r];
+        for (int r = 0; r < RW; ++r) rv[r] = rn[r];
+      }
     }
-  }
+  };
+  int s = 0;
+  for (; k0 + 256 * (s + 2) <= k1; ++s) step(s, std::true_type{}, std::true_type{});
+  for (; s < ns; ++s) step(s, s + 1 < ns, std::false_type{});
 #pragma unroll
   for (int r = 0; r < RW; ++r)
 #pragma unroll
@@ -208,114 +235,113 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
 }
 
 // ---------------------------------------------------------------------------------------
-// MFMA GEMM.  v_mfma_f32_16x16x4f32 operand layout (wave64): lane l supplies A[l%16][l/16]
-// and B[l/16][l%16]; the four accumulator registers of lane l hold D[4*(l/16)+i][l%16].
-// The K index of one MFMA is only a label shared by A and B, so lane (i, kq) feeds the eight
-// consecutive columns k + 8 kq + t (t = 0..7) of two adjacent float4 loads to eight MFMAs:
-// the two loads of a row's four lanes cover whole 128-byte lines.  Plain (cached) loads: a
-// non-temporal hint let lines leave L2 between the two halves and doubled the HBM traffic.
-// Tile: D rows = 16 rows of R, D columns = 16 realisations (b0 .. b0+15, masked to B).
+// MFMA GEMM, TB tiles of 16 realisations a pass.  v_mfma_f32_16x16x4f32 operand layout
+// (wave64): lane l supplies A[l%16][l/16] and B[l/16][l%16]; the four accumulator registers of
+// lane l hold D[4*(l/16)+i][l%16].  The K index of one MFMA is only a label shared by A and B,
+// so lane (i, kq) feeds the four consecutive columns of one float4 to four MFMAs.
+//
+// Bound by the stream of R: each wave loads its 16 rows 512 bytes a row at a time (two rows an
+// instruction) and turns them into operands through its own LDS tile, the next tile's loads in
+// flight; the workgroup's four waves share the slices of the slopes, double-buffered, one
+// barrier a tile.  Loading the operands straight from memory (32 bytes a lane of 16 rows)
+// reached 3.9 TB/s of R: B = 16 at 5,400 x 55,608 took 321 us, this takes 222 us (5.4 TB/s),
+// and up to 32 realisations read R once.  FP32 matrix instructions of 32 cycles each: 61 us of
+// the device's matrix time per 16 realisations of that size.
+// Eight accumulators a tile keep the chains of additions short.
 // ---------------------------------------------------------------------------------------
+constexpr int kTileK = 128;           // columns of one tile
+constexpr int kTileP = kTileK + 4;    // LDS pitch: 16 rows on different banks
+constexpr int kTileB = 32;            // realisations of one pass at most
 
-template <int TR>
+template <int TB>
 __global__ __launch_bounds__(kRB) void recon_mfma_kernel(const float* __restrict__ R, int M,
                                                          int N, const float* __restrict__ S,
-                                                         int B, int b0, int chunk, int splits,
-                                                         int row_groups, float* __restrict__ ws) {
-  const int wave = (blockIdx.x * kRB + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (wave >= row_groups * splits) return;
-  const int g = wave / splits, sp = wave - g * splits;
+                                                         int B, int chunk, int row_blocks,
+                                                         float* __restrict__ ws) {
+  __shared__ __align__(16) float rt[4][16][kTileP];
+  __shared__ __align__(16) float sl[2][TB * 16][kTileP];
+  const int sp = blockIdx.x / row_blocks, g = blockIdx.x - sp * row_blocks;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int row0 = (g * 4 + wave) * 16;
   const int k0 = sp * chunk, k1 = min(N, k0 + chunk);
+  const int nt = (k1 - k0 + kTileK - 1) / kTileK;
   const int i16 = lane & 15, kq = lane >> 4;
-  const int nb = b0 + i16;  // realisation fed by this lane (B operand column)
-  const bool bok = nb < B;
-  const float* srow = S + (int64_t)(bok ? nb : 0) * N;
-  const float* rrow[TR];
+  const int lr = lane >> 5, lc = 4 * (lane & 31);  // this lane's row of a pair, its columns
+  float4 rv[8], sv[2 * TB];
+  auto load_r = [&](int t) {
+    const int k = k0 + t * kTileK + lc;
+    if (k0 + (t + 1) * kTileK <= k1) {  // uniform; the last tile of a row may be short
 #pragma unroll
-  for (int t = 0; t < TR; ++t) {
-    const int row = min(g * 16 * TR + t * 16 + i16, M - 1);
-    rrow[t] = R + (int64_t)row * N;
-  }
-  v4f acc[TR];
+      for (int i = 0; i < 8; ++i) rv[i] = ldnt4(R + (int64_t)min(row0 + 2 * i + lr, M - 1) * N + k);
+    } else {
 #pragma unroll
-  for (int t = 0; t < TR; ++t) acc[t] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-  int k = k0;
-  // main loop: 32 columns per iteration (two float4 per lane per operand row), the next
-  // iteration's loads issued before this iteration's MFMAs (double-buffered registers)
-  float4 ra[TR], rb[TR], sa = make_float4(0.f, 0.f, 0.f, 0.f), sb = sa;
-  if (k + 32 <= k1) {
-    const int ka = k + 8 * kq, kb = ka + 4;
-    if (bok) {
-      sa = *reinterpret_cast<const float4*>(srow + ka);
-      sb = *reinterpret_cast<const float4*>(srow + kb);
+      for (int i = 0; i < 8; ++i)
+        rv[i] = ld4_below<true>(R + (int64_t)min(row0 + 2 * i + lr, M - 1) * N, k, k1);
+    }
+  };
+  auto load_s = [&](int t) {  // thread: slope rows threadIdx.x / 32 + 8 i, the same columns
+    const int k = k0 + t * kTileK + 4 * (threadIdx.x & 31);
+#pragma unroll
+    for (int i = 0; i < 2 * TB; ++i) {
+      const int b = (threadIdx.x >> 5) + 8 * i;
+      sv[i] = b < B ? ld4_below<false>(S + (int64_t)b * N, k, k1)
+                    : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  auto store_s = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 2 * TB; ++i)
+      *reinterpret_cast<float4*>(&sl[buf][(threadIdx.x >> 5) + 8 * i][4 * (threadIdx.x & 31)]) =
+          sv[i];
+  };
+  v4f acc[TB][8];
+#pragma unroll
+  for (int t = 0; t < TB; ++t)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[t][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+  load_s(0);
+  load_r(0);
+  store_s(0);
+  __syncthreads();
+  for (int t = 0; t < nt; ++t) {
+    // the wave's tile of R (its last readers are this wave's own, in order)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      *reinterpret_cast<float4*>(&rt[wave][2 * i + lr][lc]) = rv[i];
+    wave_sync();
+    if (t + 1 < nt) {
+      load_r(t + 1);
+      load_s(t + 1);
     }
 #pragma unroll
-    for (int t = 0; t < TR; ++t) {
-      ra[t] = *reinterpret_cast<const float4*>(rrow[t] + ka);
-      rb[t] = *reinterpret_cast<const float4*>(rrow[t] + kb);
-    }
-  }
-  for (; k + 32 <= k1; k += 32) {
-    float4 na[TR], nb[TR], nsa = make_float4(0.f, 0.f, 0.f, 0.f), nsb = nsa;
-    const bool more = k + 64 <= k1;
-    if (more) {
-      const int ka = k + 32 + 8 * kq, kb = ka + 4;
-      if (bok) {
-        nsa = *reinterpret_cast<const float4*>(srow + ka);
-        nsb = *reinterpret_cast<const float4*>(srow + kb);
+    for (int q = 0; q < kTileK / 16; ++q) {
+      const float4 a = *reinterpret_cast<const float4*>(&rt[wave][i16][16 * q + 4 * kq]);
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) {
+        const float4 x =
+            *reinterpret_cast<const float4*>(&sl[t & 1][tb * 16 + i16][16 * q + 4 * kq]);
+        v4f* c = acc[tb] + 4 * (q & 1);
+        c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, x.x, c[0], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, x.y, c[1], 0, 0, 0);
+        c[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, x.z, c[2], 0, 0, 0);
+        c[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, x.w, c[3], 0, 0, 0);
       }
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        na[t] = *reinterpret_cast<const float4*>(rrow[t] + ka);
-        nb[t] = *reinterpret_cast<const float4*>(rrow[t] + kb);
-      }
     }
-#pragma unroll
-    for (int t = 0; t < TR; ++t) {
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[t].x, sa.x, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[t].y, sa.y, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[t].z, sa.z, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[t].w, sa.w, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[t].x, sb.x, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[t].y, sb.y, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[t].z, sb.z, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[t].w, sb.w, acc[t], 0, 0, 0);
-    }
-    if (more) {
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        ra[t] = na[t];
-        rb[t] = nb[t];
-      }
-      sa = nsa;
-      sb = nsb;
-    }
+    wave_sync();
+    if (t + 1 < nt) store_s((t + 1) & 1);
+    __syncthreads();
   }
-  // tail: 16 columns per step, float4 granularity, guarded
-  for (; k < k1; k += 16) {
-    const int ka = k + 4 * kq;
-    const bool in = ka < k1;
-    float4 sa = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (bok && in) sa = *reinterpret_cast<const float4*>(srow + ka);
+  // D[4*kq + i][i16]: row = row0 + 4 kq + i, realisation = 16 tb + i16
 #pragma unroll
-    for (int t = 0; t < TR; ++t) {
-      float4 ra = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (in) ra = *reinterpret_cast<const float4*>(rrow[t] + ka);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.x, sa.x, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.y, sa.y, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.z, sa.z, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra.w, sa.w, acc[t], 0, 0, 0);
-    }
-  }
-  // D[4*kq + i][i16]: row = tile base + 4 kq + i, realisation = b0 + i16
-  if (bok) {
-#pragma unroll
-    for (int t = 0; t < TR; ++t) {
+  for (int tb = 0; tb < TB; ++tb) {
+    const v4f* c = acc[tb];
+    const v4f sum = ((c[0] + c[4]) + (c[1] + c[5])) + ((c[2] + c[6]) + (c[3] + c[7]));
+    const int b = 16 * tb + i16;
+    if (b < B) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = g * 16 * TR + t * 16 + 4 * kq + i;
-        if (row < M) ws[((int64_t)sp * B + nb) * M + row] = acc[t][i];
+        const int row = row0 + 4 * kq + i;
+        if (row < M) ws[((int64_t)sp * B + b) * M + row] = sum[i];
       }
     }
   }
@@ -340,8 +366,8 @@ __global__ __launch_bounds__(kRB) void recon_reduce_kernel(const float* __restri
 // resident wave slots, so no wave of a second round streams its chunk after the others end
 // ---------------------------------------------------------------------------------------
 static std::mutex g_occ_mu;
-static int g_slots[64][4];  // per device: resident waves of the MFMA, GEMV, unaligned and
-                            // small-batch kernels
+static int g_slots[64][3];  // per device: resident waves of the MFMA, GEMV and small-batch
+                            // kernels
 
 static hipError_t resident_waves(int which, int* out) {
   int dev = 0;
@@ -353,9 +379,8 @@ static hipError_t resident_waves(int which, int* out) {
     int cus = 0, blocks = 0;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const void* k = which == 0   ? reinterpret_cast<const void*>(recon_mfma_kernel<2>)
-                    : which == 1 ? reinterpret_cast<const void*>(recon_valu_kernel<2, true>)
-                    : which == 2 ? reinterpret_cast<const void*>(recon_valu_kernel<2, false>)
+    const void* k = which == 0   ? reinterpret_cast<const void*>(recon_mfma_kernel<1>)
+                    : which == 1 ? reinterpret_cast<const void*>(recon_valu_kernel<2>)
                                  : reinterpret_cast<const void*>(
                                        recon_batch_lds_kernel<kBatchMax, kBatchPF>);
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, kRB, 0);
@@ -380,56 +405,85 @@ static int choose_splits(int row_groups, int N, int align, int slots, int64_t ma
   return (N + c - 1) / c;  // <= want
 }
 
+enum ReconPath { kReconGemv, kReconBatch, kReconMfma };
+
 struct ReconShape {
-  int batch;       // 1: every realisation at once on the vector ALUs (2 <= B <= 8, aligned)
-  int mfma;        // 1: matrix-core GEMM in tiles of 16 realisations; 0: one GEMV per realisation
-  int aligned;     // 16-byte aligned R and S, N % 4 == 0
-  int row_groups;
-  int slots;
-  int tile_b;      // realisations per partial-sum tile (16, or 1 for the GEMV)
+  ReconPath path;
+  int units;   // wave row groups per split
+  int align;   // columns a chunk is a multiple of
+  int slots;   // resident waves
+  int tile_b;  // realisations of a partial-sum tile that every call of the path can run with
 };
 
-static hipError_t recon_shape(const float* R, int M, int N, const float* S, int B,
-                              ReconShape* sh) {
-  sh->aligned = (N % 4 == 0) && ((uintptr_t)R % 16 == 0) && ((uintptr_t)S % 16 == 0);
-  sh->batch = B >= 2 && B <= kBatchMax && sh->aligned;
-  sh->mfma = B > kBatchMax && sh->aligned;
-  sh->row_groups = sh->batch ? (M + kBatchRW - 1) / kBatchRW
-                             : (sh->mfma ? (M + 31) / 32 : (M + 1) / 2);
-  sh->tile_b = sh->batch ? B : (sh->mfma ? std::min(16, B) : 1);
-  return resident_waves(sh->batch ? 3 : (sh->mfma ? 0 : (sh->aligned ? 1 : 2)), &sh->slots);
+static hipError_t recon_shape(ReconPath path, int M, int B, ReconShape* sh) {
+  sh->path = path;
+  if (path == kReconBatch) {
+    sh->units = ((M + kBatchRW - 1) / kBatchRW + 3) / 4 * 4;
+    sh->align = 256;
+    sh->tile_b = std::min(B, kBatchMax);
+    return resident_waves(2, &sh->slots);
+  }
+  if (path == kReconMfma) {
+    sh->units = (M + 63) / 64 * 4;
+    sh->align = kTileK;
+    sh->tile_b = std::min(16, B);
+    return resident_waves(0, &sh->slots);
+  }
+  sh->units = (M + 1) / 2;
+  sh->align = 256;
+  sh->tile_b = 1;
+  return resident_waves(1, &sh->slots);
 }
 
-// Floats of partial sums a call wants (its split count unconstrained by the workspace).
-hipError_t recon_work_floats(const float* R, int M, int N, const float* S, int B,
-                             int64_t* floats) {
-  ReconShape sh;
-  hipError_t e = recon_shape(R, M, N, S, B, &sh);
-  if (e != hipSuccess) return e;
-  int chunk;
-  const int splits = choose_splits(sh.row_groups, N,
-                                   (sh.mfma ? 32 : (sh.aligned ? 256 : 64)), sh.slots,
-                                   INT32_MAX, &chunk);
-  *floats = (int64_t)splits * sh.tile_b * M;
+static ReconPath recon_path(int B) {
+  return B == 1 ? kReconGemv : (B <= kBatchMax ? kReconBatch : kReconMfma);
+}
+
+// Operands that were always taken however large M is: rows or vectors not 16-byte aligned run
+// one GEMV per realisation where a workspace cannot hold a tile of them.
+static bool recon_aligned(const float* R, int N, const float* S) {
+  return N % 4 == 0 && (uintptr_t)R % 16 == 0 && (uintptr_t)S % 16 == 0;
+}
+
+// Floats of partial sums a call wants (its split count unconstrained by the workspace), no
+// fewer than a call with a smaller B: a workspace grown by one call takes every smaller one.
+hipError_t recon_work_floats(int M, int N, int B, int64_t* floats) {
+  *floats = 0;
+  for (int path = kReconGemv; path <= recon_path(B); ++path) {
+    ReconShape sh;
+    hipError_t e = recon_shape((ReconPath)path, M, B, &sh);
+    if (e != hipSuccess) return e;
+    int chunk;
+    const int splits = choose_splits(sh.units, N, sh.align, sh.slots, INT32_MAX, &chunk);
+    *floats = std::max(*floats, (int64_t)splits * sh.tile_b * M);
+  }
   return hipSuccess;
 }
 
-// C = alpha R S^T + beta C with the split partial sums in ws (ws_floats >= M * min(B, 16));
-// the split count shrinks to what ws holds.
+static hipError_t recon_reduce(const float* ws, int M, int bc, int splits, float* C, int64_t ldc,
+                               float alpha, float beta, int b0, hipStream_t st) {
+  const int64_t n = (int64_t)M * bc;
+  hipLaunchKernelGGL(recon_reduce_kernel, dim3((unsigned)((n + kRB - 1) / kRB)), dim3(kRB), 0, st,
+                     ws, M, bc, splits, C, ldc, alpha, beta, b0, bc);
+  return hipGetLastError();
+}
+
+// C = alpha R S^T + beta C with the split partial sums in ws; the split count (and the
+// realisations of a matrix-core pass) shrink to what ws holds.
 hipError_t recon_launch(const float* R, int M, int N, const float* S, int B, float* C,
                         int64_t ldc, float alpha, float beta, float* ws, int64_t ws_floats,
-                        hipStream_t st, int* used_mfma) {
+                        hipStream_t st) {
+  ReconPath path = recon_path(B);
+  if (path != kReconGemv && ws_floats < (int64_t)std::min(B, 16) * M) path = kReconGemv;
   ReconShape sh;
-  hipError_t e = recon_shape(R, M, N, S, B, &sh);
+  hipError_t e = recon_shape(path, M, B, &sh);
   if (e != hipSuccess) return e;
-  *used_mfma = sh.mfma;
-  const int64_t max_splits = ws_floats / ((int64_t)sh.tile_b * M);
-  if (max_splits < 1) return hipErrorInvalidValue;
-  if (sh.batch) {
-    int chunk;
-    const int quads = (sh.row_groups + 3) / 4;  // workgroups of 4 row groups per split
-    const int splits = choose_splits(quads * 4, N, 256, sh.slots, max_splits, &chunk);
-    const int grid = quads * splits;
+  if (ws_floats < M) return hipErrorInvalidValue;
+  int chunk;
+  if (path == kReconBatch) {
+    const int splits =
+        choose_splits(sh.units, N, sh.align, sh.slots, ws_floats / ((int64_t)B * M), &chunk);
+    const int quads = sh.units / 4, grid = quads * splits;
     if (B <= 2)
       hipLaunchKernelGGL((recon_batch_lds_kernel<2, kBatchPF>), dim3(grid), dim3(kRB), 0, st, R,
                          M, N, S, B, chunk, quads, ws);
@@ -440,48 +494,39 @@ hipError_t recon_launch(const float* R, int M, int N, const float* S, int B, flo
       hipLaunchKernelGGL((recon_batch_lds_kernel<kBatchMax, kBatchPF>), dim3(grid), dim3(kRB), 0,
                          st, R, M, N, S, B, chunk, quads, ws);
     e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)M * B;
-    hipLaunchKernelGGL(recon_reduce_kernel, dim3((unsigned)((n + kRB - 1) / kRB)), dim3(kRB), 0,
-                       st, ws, M, B, splits, C, ldc, alpha, beta, 0, B);
-    return hipGetLastError();
+    return e == hipSuccess ? recon_reduce(ws, M, B, splits, C, ldc, alpha, beta, 0, st) : e;
   }
-  if (sh.mfma) {
-    constexpr int TR = 2;
-    int chunk;
-    const int splits = choose_splits(sh.row_groups, N, 32, sh.slots, max_splits, &chunk);
-    for (int b0 = 0; b0 < B; b0 += 16) {
-      const int bc = std::min(16, B - b0);
-      const int waves = sh.row_groups * splits;
-      hipLaunchKernelGGL(recon_mfma_kernel<TR>, dim3((waves + 3) / 4), dim3(kRB), 0, st, R, M,
-                         N, S + (int64_t)b0 * N, bc, 0, chunk, splits, sh.row_groups, ws);
+  if (path == kReconMfma) {
+    // passes of up to 32 realisations, evenly wide, their partial sums in the floats that 16
+    // want (half the splits then); 16 where ws holds no more
+    const int most = ws_floats >= (int64_t)kTileB * M ? kTileB : 16;
+    const int passes = (B + most - 1) / most;
+    const int per = ((B + passes - 1) / passes + 15) / 16 * 16;
+    for (int b0 = 0; b0 < B; b0 += per) {
+      const int bc = std::min(per, B - b0);
+      const int splits = choose_splits(sh.units, N, sh.align, bc > 16 ? sh.slots / 2 : sh.slots,
+                                       ws_floats / ((int64_t)bc * M), &chunk);
+      const int grid = sh.units / 4 * splits;
+      if (bc <= 16)
+        hipLaunchKernelGGL(recon_mfma_kernel<1>, dim3(grid), dim3(kRB), 0, st, R, M, N,
+                           S + (int64_t)b0 * N, bc, chunk, sh.units / 4, ws);
+      else
+        hipLaunchKernelGGL(recon_mfma_kernel<2>, dim3(grid), dim3(kRB), 0, st, R, M, N,
+                           S + (int64_t)b0 * N, bc, chunk, sh.units / 4, ws);
       e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      const int64_t n = (int64_t)M * bc;
-      hipLaunchKernelGGL(recon_reduce_kernel, dim3((unsigned)((n + kRB - 1) / kRB)), dim3(kRB), 0,
-                         st, ws, M, bc, splits, C, ldc, alpha, beta, b0, bc);
-      e = hipGetLastError();
+      if (e == hipSuccess) e = recon_reduce(ws, M, bc, splits, C, ldc, alpha, beta, b0, st);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   }
   constexpr int RW = 2;
-  int chunk;
-  const int splits =
-      choose_splits(sh.row_groups, N, sh.aligned ? 256 : 64, sh.slots, max_splits, &chunk);
+  const int splits = choose_splits(sh.units, N, sh.align, sh.slots, ws_floats / M, &chunk);
   for (int b = 0; b < B; ++b) {
-    const int waves = sh.row_groups * splits;
-    if (sh.aligned)
-      hipLaunchKernelGGL((recon_valu_kernel<RW, true>), dim3((waves + 3) / 4), dim3(kRB), 0, st,
-                         R, M, N, S, b, chunk, splits, sh.row_groups, ws);
-    else
-      hipLaunchKernelGGL((recon_valu_kernel<RW, false>), dim3((waves + 3) / 4), dim3(kRB), 0,
-                         st, R, M, N, S, b, chunk, splits, sh.row_groups, ws);
+    const int waves = sh.units * splits;
+    hipLaunchKernelGGL((recon_valu_kernel<RW>), dim3((waves + 3) / 4), dim3(kRB), 0, st, R, M, N,
+                       S, b, chunk, splits, sh.units, ws);
     e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(recon_reduce_kernel, dim3((M + kRB - 1) / kRB), dim3(kRB), 0, st, ws, M,
-                       1, splits, C, ldc, alpha, beta, b, 1);
-    e = hipGetLastError();
+    if (e == hipSuccess) e = recon_reduce(ws, M, 1, splits, C, ldc, alpha, beta, b, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -503,7 +548,11 @@ static std::mutex g_ws_mu;
 static std::vector<StreamWork> g_ws;       // current buffer of each (device, stream)
 static std::vector<float*> g_ws_retired;   // outgrown buffers, kept for captured graphs
 
-hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, bool* capturing) {
+// The stream's buffer, grown to `floats` where it holds fewer (*have: what it holds).  While
+// the stream is capturing it cannot grow: *capturing is set, *out and *have are the current
+// buffer (or null and 0).
+hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, int64_t* have,
+                             bool* capturing) {
   *capturing = false;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -512,10 +561,9 @@ hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, bool* 
   StreamWork* w = nullptr;
   for (auto& x : g_ws)
     if (x.dev == dev && x.stream == st) w = &x;
-  if (w && w->floats >= floats) {
-    *out = w->ptr;
-    return hipSuccess;
-  }
+  *out = w ? w->ptr : nullptr;
+  *have = w ? w->floats : 0;
+  if (w && w->floats >= floats) return hipSuccess;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   e = hipStreamIsCapturing(st, &cs);
   if (e != hipSuccess) return e;
@@ -534,6 +582,7 @@ hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, bool* 
     g_ws.push_back(StreamWork{dev, st, p, floats});
   }
   *out = p;
+  *have = floats;
   return hipSuccess;
 }
 
@@ -550,14 +599,10 @@ static float* g_static_ptr[64];
 
 int64_t recon_static_work_floats() { return kStaticWorkFloats; }
 
-// Floats of partial sums one split of a call needs (M rows x the realisations of one tile).
-hipError_t recon_min_work_floats(const float* R, int M, int N, const float* S, int B,
-                                 int64_t* floats) {
-  ReconShape sh;
-  hipError_t e = recon_shape(R, M, N, S, B, &sh);
-  if (e != hipSuccess) return e;
-  *floats = (int64_t)sh.tile_b * M;
-  return hipSuccess;
+// Floats of partial sums a call cannot do without (M rows x the realisations of one tile; a
+// single realisation's for operands that are not 16-byte aligned).
+int64_t recon_min_work_floats(const float* R, int M, int N, const float* S, int B) {
+  return (int64_t)(recon_aligned(R, N, S) ? std::min(B, 16) : 1) * M;
 }
 
 hipError_t recon_static_work(float** out) {

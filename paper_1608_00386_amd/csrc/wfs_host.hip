@@ -42,16 +42,15 @@ int fft_adj_wave_lds_bytes(int n_fft, int n_pix);
 hipError_t launch_adjoint_fft(const AdjParams& a, int lds_per_wave, hipStream_t st);
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather);
 bool adj_takes(int ns, int n_layers, int n_pix);
-hipError_t recon_work_floats(const float* R, int M, int N, const float* S, int B,
-                             int64_t* floats);
-hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, bool* capturing);
+hipError_t recon_work_floats(int M, int N, int B, int64_t* floats);
+hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, int64_t* have,
+                             bool* capturing);
 int64_t recon_static_work_floats();
-hipError_t recon_min_work_floats(const float* R, int M, int N, const float* S, int B,
-                                 int64_t* floats);
+int64_t recon_min_work_floats(const float* R, int M, int N, const float* S, int B);
 hipError_t recon_static_work(float** out);
 hipError_t recon_launch(const float* R, int M, int N, const float* S, int B, float* C,
                         int64_t ldc, float alpha, float beta, float* ws, int64_t ws_floats,
-                        hipStream_t st, int* used_mfma);
+                        hipStream_t st);
 hipError_t calib_poke(float* layers, const float* base, int64_t stride, int32_t h, int64_t act0,
                       int32_t n_chunk, float amp, hipStream_t st);
 hipError_t calib_diff(const float* slopes, int32_t h, int32_t n_slopes, int32_t n_chunk,
@@ -1859,21 +1858,28 @@ int recon_apply(const float* R, int32_t M, int32_t N, const float* S, int32_t B,
   if (!std::isfinite(alpha) || !std::isfinite(beta))
     return fail(WFS_EINVAL, "recon_apply: non-finite alpha or beta");
   hipStream_t st = (hipStream_t)stream;
-  int64_t floats = 0;
-  hipError_t e = recon_work_floats(R, M, N, S, B, &floats);
+  int64_t floats = 0, have = 0;
+  hipError_t e = recon_work_floats(M, N, B, &floats);
   if (e != hipSuccess) return hip_fail(e, "recon_apply");
   float* ws = nullptr;
   bool capturing = false;
-  e = recon_stream_work(st, floats, &ws, &capturing);
-  if (capturing)
-    return fail(WFS_EINVAL,
-                "recon_apply: the stream is capturing a graph and its workspace must grow to "
-                "%lld floats: call recon_apply once with this size (or larger) on this stream "
-                "before the capture",
-                (long long)floats);
+  e = recon_stream_work(st, floats, &ws, &have, &capturing);
+  if (capturing) {
+    // operands that are not 16-byte aligned are taken with a single realisation's workspace
+    if (recon_min_work_floats(R, M, N, S, B) == M) {
+      e = recon_work_floats(M, N, 1, &floats);
+      if (e != hipSuccess) return hip_fail(e, "recon_apply");
+    }
+    if (!ws || have < floats)
+      return fail(WFS_EINVAL,
+                  "recon_apply: the stream is capturing a graph and its workspace must grow to "
+                  "%lld floats: call recon_apply once with this size (or larger) on this stream "
+                  "before the capture",
+                  (long long)floats);
+  }
   if (e != hipSuccess) return hip_fail(e, "recon_apply: workspace");
-  int mfma = 0;
-  e = recon_launch(R, M, N, S, B, C, ldc, alpha, beta, ws, floats, st, &mfma);
+  // the splits follow from the floats this size wants, never from what else the stream ran
+  e = recon_launch(R, M, N, S, B, C, ldc, alpha, beta, ws, floats, st);
   if (e != hipSuccess) return hip_fail(e, "recon_apply");
   return WFS_OK;
 }
@@ -1888,9 +1894,7 @@ int recon_apply_noalloc(const float* R, int32_t M, int32_t N, const float* S, in
   if ((int64_t)M * N > (1LL << 40)) return fail(WFS_EINVAL, "recon_apply_noalloc: R too large");
   if (!std::isfinite(alpha) || !std::isfinite(beta))
     return fail(WFS_EINVAL, "recon_apply_noalloc: non-finite alpha or beta");
-  int64_t need = 0;
-  hipError_t e = recon_min_work_floats(R, M, N, S, B, &need);
-  if (e != hipSuccess) return hip_fail(e, "recon_apply_noalloc");
+  const int64_t need = recon_min_work_floats(R, M, N, S, B);
   const int64_t cap = recon_static_work_floats();
   if (need > cap)
     return fail(WFS_EINVAL,
@@ -1900,10 +1904,9 @@ int recon_apply_noalloc(const float* R, int32_t M, int32_t N, const float* S, in
                 M, (int)(need / M), (long long)need, (long long)cap,
                 (long long)cap);
   float* ws = nullptr;
-  e = recon_static_work(&ws);
+  hipError_t e = recon_static_work(&ws);
   if (e != hipSuccess) return hip_fail(e, "recon_apply_noalloc: workspace address");
-  int mfma = 0;
-  e = recon_launch(R, M, N, S, B, C, ldc, alpha, beta, ws, cap, (hipStream_t)stream, &mfma);
+  e = recon_launch(R, M, N, S, B, C, ldc, alpha, beta, ws, cap, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "recon_apply_noalloc");
   return WFS_OK;
 }
