@@ -23,6 +23,8 @@
 //     pupil pixels from per-step lists (one small kernel per call builds them, the gather
 //     then needs no FP64 and no searches); the others search their candidates per tile;
 //   atomic scatter: each pupil pixel adds its four weighted taps with FP32 atomics.
+#include <utility>
+
 #include "wfs_fft.h"
 #include "wfs_otf.h"
 
@@ -444,31 +446,62 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_kernel(GatherParams
 // Table-driven gather (layers whose inverse stencil lists are short: pupil and layer pitches
 // within a factor of about two, one periodic image per layer pixel).
 //
-// Taps kernel, thread per (segment, layer index i): the pupil indices whose forward taps (the
-// same FP64 coordinate and make_tap as the projection, bit for bit) touch i, in increasing
-// order, with the weight i has in their stencil.  Candidates: for every periodic image m, the
-// indices whose coordinate lies in [i - 1 + m n, i + 1 + m n), with a margin of one index.
+// Taps kernel, thread per (segment, index i), from the same FP64 coordinate and make_tap as the
+// projection, bit for bit.  Column segments: the pupil columns whose forward taps touch layer
+// column i, in increasing order, with the weight i has in their stencil.  Row segments: the
+// pupil rows whose first tap row is i - 1 (a zero boundary's taps -1 .. ny - 1; a periodic
+// one's last row is also its row -1), at most two as the pupil rows lie more than half a layer
+// row apart, with both weights.  Candidates: for every periodic image m, the indices whose
+// coordinate lies in [i - 1 + m n, i + 1 + m n), with a margin of one index.
 // ---------------------------------------------------------------------------------------
+constexpr int kG2R = 16;  // layer rows of a wave
+constexpr int kG2TH = kG2R * kWavesPerBlock;
+
+// Entry of the row table, base = entry - 1: the byte offset of the first pupil row in the
+// sensor's image, the bytes to the second, and their weights on layer rows base (w0) and base +
+// 1 (w1).  A single row stands for both with half of its weights, so the gather has no branch
+// for it; n = 0: no row (offsets 0, not used).
+struct RowEnt {
+  int32_t off_lo, off_hi, step, n;
+  float w0a, w1a, w0b, w1b;
+};
+static_assert(sizeof(RowEnt) == 4 * sizeof(int2), "row entries fill whole int2 entries");
+
+__host__ __device__ inline int row_ents(int ny) { return (ny + kG2R - 1) / kG2R * kG2R + 2; }
+
+// The table entries (int2) and threads of a (sensor, layer)'s row segment.
+int adj_row_ents(int ny) { return row_ents(ny); }
+int64_t adj_row_int2(int ny) { return (int64_t)row_ents(ny) * (sizeof(RowEnt) / sizeof(int2)); }
+
 __global__ __launch_bounds__(kBlock) void wfs_adjoint_taps_kernel(GatherTabParams g) {
   const FwdParams& p = g.f;
   const AdjSeg sg = g.segs[blockIdx.y];
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= sg.n) return;
+  int i = blockIdx.x * kBlock + threadIdx.x;
+  const bool ax = sg.axis == 0;
+  if (i >= (ax ? sg.n : row_ents(sg.n))) return;
   const DevLayer L = p.lay[sg.l];
   const DevAffine A = p.aff[(int64_t)sg.s * p.n_layers + sg.l];
   const int npup = p.sen[sg.s].n_pup;
   const double stepd = (double)current_step(p);
-  const bool ax = sg.axis == 0;
   const double a = ax ? A.ax : A.ay, b0 = ax ? A.bx0 : A.by0, db = ax ? A.dbx : A.dby;
   const double inv_a = ax ? A.inv_ax : A.inv_ay;
   const int32_t n = ax ? L.nx : L.ny;
   const double inv_n = ax ? L.inv_nx : L.inv_ny;
   const double b = b0 + stepd * db;
+  RowEnt* const row_dst = reinterpret_cast<RowEnt*>(g.tab + sg.off) + i;
+  if (!ax) {
+    i = i == 0 ? (L.boundary == 0 ? n - 1 : -1) : i - 1;
+    if (i >= n) {
+      *row_dst = RowEnt{};
+      return;
+    }
+  }
   int m_lo, m_hi;
   image_range(a, b, n, inv_n, npup, i, i, L.boundary, m_lo, m_hi);
   int2 out[kAdjKI];
 #pragma unroll
   for (int k = 0; k < kAdjKI; ++k) out[k] = make_int2(-1, 0);
+  RowEnt re{};
   int cnt = 0;
   for (int m = m_lo; m <= m_hi; ++m) {
     int lo, hi;
@@ -477,6 +510,24 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_taps_kernel(GatherTabParam
     for (int c = lo; c <= hi; ++c) {
       const double w = fma(a, (double)c, b0) + stepd * db;
       const Tap t = make_tap(w, n, inv_n, L.boundary, 1);
+      if (!ax) {
+        if ((L.boundary == 0 ? t.i0 : (int)floor(w)) != i || re.n == 2) continue;
+        if (re.n == 0) {
+          const int64_t off = 4 * (int64_t)c * npup;
+          re.off_lo = (int32_t)(uint32_t)off;
+          re.off_hi = (int32_t)(off >> 32);
+          re.w0a = re.w0b = 0.5f * t.w0;
+          re.w1a = re.w1b = 0.5f * t.w1;
+        } else {
+          re.step = 4 * npup;
+          re.w0a *= 2.0f;
+          re.w1a *= 2.0f;
+          re.w0b = t.w0;
+          re.w1b = t.w1;
+        }
+        ++re.n;
+        continue;
+      }
       const float wt = (t.i0 == i ? t.w0 : 0.0f) + (t.i1 == i ? t.w1 : 0.0f);
       if (wt != 0.0f && cnt < kAdjKI) {
 #pragma unroll
@@ -486,29 +537,112 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_taps_kernel(GatherTabParam
       }
     }
   }
+  if (!ax) {
+    *row_dst = re;
+    return;
+  }
   int2* dst = g.tab + sg.off + (int64_t)i * kAdjKI;
 #pragma unroll
   for (int k = 0; k < kAdjKI; ++k) dst[k] = out[k];
 }
 
 // Gather kernel for tabled layers (one periodic image per layer pixel: for every sensor the
-// pupil rows touching a run of layer rows are consecutive, and so are the pupil columns of
-// one layer column).  Block = (realisation, tabled layer, 64 x 64 tile); wave = 64 layer
-// columns (one per lane) x kG2R rows, accumulated in the wave's own LDS rows (the waves never
-// wait for each other).  For every sensor in order, each pupil row r whose taps reach the
-// wave's rows is reduced along the lane's column list,
-//     T = sum_j wc_j g[r][cf + j],
-// and added to the (at most two) layer rows of its forward row tap with that tap's weights
-// (the same FP64 coordinate and make_tap as the projection).  Fixed order of every sum:
-// bitwise deterministic.
-constexpr int kG2R = 16;
-constexpr int kG2TH = kG2R * kWavesPerBlock;
-constexpr int kG2MaxPR = 64;  // pupil rows per sensor and wave (above: direct per-row lists)
-constexpr int kG2Chunk = 8;   // pupil rows whose loads are in flight together
+// pupil columns of one layer column are consecutive).  Block = (realisation, tabled layer,
+// 64 x 64 tile); wave = 64 layer columns (one per lane) x kG2R rows, accumulated in registers.
+// For every sensor in order the pupil rows are summed into the wave's layer rows first, lane =
+// pupil column, and the columns of each lane's list then, through LDS: fixed order of every
+// sum, bitwise deterministic.
+//
+// Bound by vector issue and latency (six 80 x 80 LGS and ten 1024^2 layers: 15 MB read, 42 MB
+// written, 12 us at the copy rate).  Loading each lane's own columns from memory took 120 us
+// however the sums were organised: 64 lanes whose addresses are not strictly consecutive go
+// through the cache a quad a cycle, 16 cycles a load instead of 4.  Loading the rows as they lie
+// and picking columns from LDS, with row taps from scalar loads: 53 us.
+
+// f(0), ..., f(N - 1) as compile-time constants: the arrays they index stay in registers.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+constexpr int kG2Cols = 2 * kWave;  // pupil columns of a window
+
+// One sensor's rows over a window of pupil columns, lane holding columns col[0] and col[1]
+// (window positions lane and lane + 64).  Its first tap rows -1 .. kG2R - 1 go by in pairs, the
+// pupil rows of the next pair in flight while one is summed into the layer rows (over the
+// window's columns), their entries a pair further ahead.  Every four finished layer rows pass
+// through LDS, where a lane reads its NC columns from position at.
+template <int NC>
+__device__ __forceinline__ void gather_rows(const float* gs, const RowEnt* ents,
+                                            const uint32_t (&col)[2], int lane, int at,
+                                            const float (&wc)[kAdjKI], float4* buf,
+                                            float (&acc)[kG2R]) {
+  constexpr int CH = 2, NG = (kG2R + CH) / CH;
+  struct Ents {
+    RowEnt e[CH];
+  };
+  const Ents* eg = reinterpret_cast<const Ents*>(ents);
+  Ents es[3];
+  float v[2][CH][2][2], r[kG2R + 2][2];
+  auto load = [&](auto g) __attribute__((always_inline)) {
+    // (opaque: a 32-bit lane offset seen here goes with a scalar base into the load)
+    uint32_t c[2] = {col[0], col[1]};
+    asm("" : "+v"(c[0]), "+v"(c[1]));
+    static_for<CH>([&](auto k) __attribute__((always_inline)) {
+      const RowEnt& e = es[g % 3].e[k];
+      const char* ga = reinterpret_cast<const char*>(gs) +
+                       (int64_t)(((uint64_t)(uint32_t)e.off_hi << 32) | (uint32_t)e.off_lo);
+      const char* gb = ga + (uint32_t)e.step;
+      static_for<2>([&](auto h) __attribute__((always_inline)) {
+        v[g & 1][k][0][h] = ld_idx(reinterpret_cast<const float*>(ga), c[h]);
+        v[g & 1][k][1][h] = ld_idx(reinterpret_cast<const float*>(gb), c[h]);
+      });
+    });
+  };
+  es[0] = cload(eg, 0);
+  es[1] = cload(eg, 1);
+  load(std::integral_constant<int, 0>{});
+  r[1][0] = r[1][1] = 0.0f;
+  static_for<NG>([&](auto g) __attribute__((always_inline)) {
+    if constexpr (g + 1 < NG) load(std::integral_constant<int, g + 1>{});
+    if constexpr (g + 2 < NG) es[(g + 2) % 3] = cload(eg, g + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<CH>([&](auto k) __attribute__((always_inline)) {
+      constexpr int row = g * CH + k;  // r[row]: layer row y0 + row - 1
+      if constexpr (row <= kG2R) {
+        const RowEnt& e = es[g % 3].e[k];
+        static_for<2>([&](auto h) __attribute__((always_inline)) {
+          // (not a weight of zero where there is no row: the one read may hold an infinity)
+          const float a = e.n ? v[g & 1][k][0][h] : 0.0f, b = e.n ? v[g & 1][k][1][h] : 0.0f;
+          if constexpr (row > 0) r[row][h] = fmaf(e.w0b, b, fmaf(e.w0a, a, r[row][h]));
+          r[row + 1][h] = fmaf(e.w1b, b, e.w1a * a);
+        });
+        if constexpr (row > 0 && row % 4 == 0) {
+          buf[lane] = make_float4(r[row - 3][0], r[row - 2][0], r[row - 1][0], r[row][0]);
+          buf[lane + kWave] = make_float4(r[row - 3][1], r[row - 2][1], r[row - 1][1], r[row][1]);
+          wave_sync();
+          float4 x[NC];
+          static_for<NC>([&](auto q) __attribute__((always_inline)) { x[q] = buf[at + q]; });
+          static_for<NC>([&](auto q) __attribute__((always_inline)) {
+            acc[row - 4] = fmaf(wc[q], x[q].x, acc[row - 4]);
+            acc[row - 3] = fmaf(wc[q], x[q].y, acc[row - 3]);
+            acc[row - 2] = fmaf(wc[q], x[q].z, acc[row - 2]);
+            acc[row - 1] = fmaf(wc[q], x[q].w, acc[row - 1]);
+          });
+          wave_sync();
+        }
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
 
 __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTabParams g) {
-  __shared__ float acc_s[kWavesPerBlock][kG2R][kWave];
-  __shared__ float4 rtap_s[kWavesPerBlock][kG2MaxPR];  // (row - y0 of tap 0, of tap 1, w0, w1)
+  __shared__ float4 buf_s[kWavesPerBlock][kG2Cols + kAdjKI];  // (the last: zero)
   const FwdParams& p = g.f;
   const int nl = p.n_layers;
   const int per_real = g.blk_start[nl];
@@ -527,22 +661,31 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTa
   const int nrows = min(kG2R, L.ny - y0);  // wave-uniform, may be <= 0
   if (nrows <= 0) return;                  // no block-wide barrier below
   const bool xin = x < L.nx;
-  float* acc = &acc_s[wave][0][0];
-  float4* rtap = rtap_s[wave];
-#pragma unroll
-  for (int yy = 0; yy < kG2R; ++yy) acc[yy * kWave + lane] = 0.0f;
+  float4* buf = buf_s[wave];
+  if (lane < kAdjKI) buf[kG2Cols + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float acc[kG2R];
+  static_for<kG2R>([&](auto yy) __attribute__((always_inline)) { acc[yy] = 0.0f; });
   const float* gb = g.gpsi + (int64_t)b * p.pupil_per_real;
-  const double stepd = (double)current_step(p);
   const int xl = xin ? x : 0;
-  // the lane's column list of a sensor: consecutive pupil columns from its first entry, with
-  // their weights (0 past the list's end); the next sensor's list is loaded while this one's
-  // rows are summed
+  // of a sensor: the lane's column list (consecutive pupil columns from its first entry, with
+  // their weights, 0 past the list's end), the number of pupil rows of the wave's first tap
+  // row -1 + lane, where its row entries and its image are; loaded while the sensor before it
+  // is summed
   int2 ce[kAdjKI];
-  {
-    const int2* e0 = g.tab + g.tab_off[l] + (int64_t)xl * kAdjKI;
+  int en, npup;
+  const RowEnt* ents;
+  const float* gs;
+  auto fetch = [&](int s) __attribute__((always_inline)) {
+    const int2* e0 = g.tab + cload(g.tab_off, (int64_t)s * nl + l);
 #pragma unroll
-    for (int k = 0; k < kAdjKI; ++k) ce[k] = e0[k];
-  }
+    for (int k = 0; k < kAdjKI; ++k) ce[k] = e0[(int64_t)xl * kAdjKI + k];
+    ents = reinterpret_cast<const RowEnt*>(e0 + (int64_t)L.nx * kAdjKI) + y0;
+    en = ents[min(lane, kG2R)].n;
+    const DevSensor S = cload(p.sen, s);
+    gs = gb + S.pupil_off;
+    npup = S.n_pup;
+  };
+  fetch(0);
   for (int s = 0; s < p.n_sensors; ++s) {
     float wc[kAdjKI];
     int cf = 0, ncol = 0;
@@ -553,97 +696,38 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTa
       wc[k] = ok ? __int_as_float(ce[k].y) : 0.0f;
       if (__builtin_amdgcn_ballot_w64(ok) != 0) ncol = k + 1;  // wave-uniform
     }
-    if (s + 1 < p.n_sensors) {
-      const int2* e1 = g.tab + g.tab_off[(int64_t)(s + 1) * nl + l] + (int64_t)xl * kAdjKI;
-#pragma unroll
-      for (int k = 0; k < kAdjKI; ++k) ce[k] = e1[k];
-    }
-    const DevSensor S = cload(p.sen, s);
-    const DevAffine A = cload(p.aff, (int64_t)s * nl + l);
-    const float* gs = gb + S.pupil_off;
-    const int npup = S.n_pup;
-    // pupil rows whose taps can reach the wave's rows, every periodic image (FP64, the
-    // candidate rule of the taps kernel: one index of slack on each side)
-    const double by = A.by0 + stepd * A.dby;
-    int m_lo, m_hi;
-    image_range(A.ay, by, L.ny, L.inv_ny, npup, y0, y0 + nrows - 1, L.boundary, m_lo, m_hi);
-    int r_lo = 0x7FFFFFFF, r_hi = -1;
-    for (int m = m_lo; m <= m_hi; ++m) {
-      int lo, hi;
-      const double base = (double)m * (double)L.ny;
-      cand_range(A.inv_ay, by, base + y0, base + y0 + nrows - 1, npup, lo, hi);
-      if (lo <= hi) {
-        r_lo = min(r_lo, lo);
-        r_hi = max(r_hi, hi);
-      }
-    }
-    if (r_hi < r_lo || ncol == 0) continue;  // wave-uniform: no contribution
-    const int nr = r_hi - r_lo + 1;
-    if (nr <= kG2MaxPR) {
-      // forward row taps of those pupil rows, relative to y0
-      if (lane < nr) {
-        const double v = fma(A.ay, (double)(r_lo + lane), A.by0) + stepd * A.dby;
-        const Tap t = make_tap(v, L.ny, L.inv_ny, L.boundary, 1);
-        rtap[lane] = make_float4(__int_as_float(t.i0 - y0), __int_as_float(t.i1 - y0), t.w0,
-                                 t.w1);
-      }
-      wave_sync();
-      int cq[kAdjKI];
-#pragma unroll
-      for (int q = 0; q < kAdjKI; ++q) cq[q] = min(cf + q, npup - 1);
-      const float* gr0 = gs + (int64_t)r_lo * npup;
-      // chunks of kG2Chunk pupil rows: every load of a chunk in flight before its sums (double
-      // buffering the chunks measured slower: the registers cost more occupancy than it hid)
-      for (int j0 = 0; j0 < nr; j0 += kG2Chunk) {
-        float v[kG2Chunk][kAdjKI];
-#pragma unroll
-        for (int jj = 0; jj < kG2Chunk; ++jj) {
-          const float* gr = gr0 + (int64_t)min(j0 + jj, nr - 1) * npup;
-#pragma unroll
-          for (int q = 0; q < kAdjKI; ++q) v[jj][q] = q < ncol ? gr[cq[q]] : 0.0f;
-        }
-#pragma unroll
-        for (int jj = 0; jj < kG2Chunk; ++jj) {
-          if (j0 + jj >= nr) break;
-          float t = 0.0f;
-#pragma unroll
-          for (int q = 0; q < kAdjKI; ++q)
-            if (q < ncol) t = fmaf(wc[q], v[jj][q], t);
-          const float4 tp = rtap[j0 + jj];  // wave-uniform (broadcast)
-          const int r0 = __builtin_amdgcn_readfirstlane(__float_as_int(tp.x));
-          const int r1 = __builtin_amdgcn_readfirstlane(__float_as_int(tp.y));
-          if (r0 >= 0 && r0 < nrows)
-            acc[r0 * kWave + lane] = fmaf(tp.z, t, acc[r0 * kWave + lane]);
-          if (r1 >= 0 && r1 < nrows)
-            acc[r1 * kWave + lane] = fmaf(tp.w, t, acc[r1 * kWave + lane]);
-        }
-      }
-      wave_sync();  // the next sensor rewrites the taps
-    } else {
-      // the wave's rows take pupil rows from two periodic images: each layer row walks its
-      // own list
-      const int2* rows = g.tab + g.tab_off[(int64_t)s * nl + l] + (int64_t)L.nx * kAdjKI;
-      for (int yy = 0; yy < nrows; ++yy) {
-        float a = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kAdjKI; ++k) {
-          const int2 e = rows[(int64_t)(y0 + yy) * kAdjKI + k];
-          if (e.x < 0) break;
-          const float* gr = gs + (int64_t)e.x * npup;
-          float t = 0.0f;
-#pragma unroll
-          for (int q = 0; q < kAdjKI; ++q)
-            if (q < ncol) t = fmaf(wc[q], gr[min(cf + q, npup - 1)], t);
-          a = fmaf(__int_as_float(e.y), t, a);
-        }
-        acc[yy * kWave + lane] += a;
-      }
+    if (__builtin_amdgcn_ballot_w64(en != 0) == 0) ncol = 0;
+    const RowEnt* const ents_s = ents;
+    const float* const gs_s = gs;
+    const int npup_s = npup;
+    if (s + 1 < p.n_sensors) fetch(s + 1);
+    if (ncol == 0) continue;  // wave-uniform: no contribution
+    // windows of pupil columns from the first lane's that is not done: one, or two where the
+    // wave's columns hold both ends of a periodic footprint (the columns increase but there;
+    // 64 layer columns touch fewer than 64 * 3 / 2 + 4 pupil columns)
+    uint64_t left = __builtin_amdgcn_ballot_w64(wc[0] != 0.0f);
+    while (left != 0) {
+      const int c0 = __builtin_amdgcn_readlane(cf, __builtin_ctzll(left));
+      const bool part = ((left >> lane) & 1) && cf >= c0 && cf + ncol <= c0 + kG2Cols;
+      left &= ~__builtin_amdgcn_ballot_w64(part);
+      const int at = part ? cf - c0 : kG2Cols;
+      const uint32_t col[2] = {(uint32_t)min(c0 + lane, npup_s - 1),
+                               (uint32_t)min(c0 + kWave + lane, npup_s - 1)};
+      if (ncol == 1)
+        gather_rows<1>(gs_s, ents_s, col, lane, at, wc, buf, acc);
+      else if (ncol == 2)
+        gather_rows<2>(gs_s, ents_s, col, lane, at, wc, buf, acc);
+      else if (ncol == 3)
+        gather_rows<3>(gs_s, ents_s, col, lane, at, wc, buf, acc);
+      else
+        gather_rows<4>(gs_s, ents_s, col, lane, at, wc, buf, acc);
     }
   }
   if (xin) {
     float* out = g.grad + (int64_t)b * p.layer_stride + L.offset + x;
-    for (int yy = 0; yy < nrows; ++yy)
-      out[(int64_t)(y0 + yy) * L.nx] = acc[yy * kWave + lane] * L.weight;
+    static_for<kG2R>([&](auto yy) __attribute__((always_inline)) {
+      if (yy < nrows) out[(int64_t)(y0 + yy) * L.nx] = acc[yy] * L.weight;
+    });
   }
 }
 
@@ -738,6 +822,7 @@ hipError_t launch_adjoint_gather_tab(const FwdParams& f, const float* gpsi, floa
 }
 
 int adj_tab_rows() { return kG2TH; }
+
 
 // FFT-path sensors: one wave per spectrum chunk (fft_adjoint_chunk_m), after the clear of the
 // phase-gradient images and before the gather

@@ -38,6 +38,8 @@ hipError_t launch_adjoint_gather_tab(const FwdParams& f, const float* gpsi, floa
                                      const int64_t* tab_off, const int32_t* blk_start,
                                      hipStream_t st);
 int adj_tab_rows();
+int adj_row_ents(int ny);
+int64_t adj_row_int2(int ny);
 int fft_adj_wave_lds_bytes(int n_fft, int n_pix);
 hipError_t launch_adjoint_fft(const AdjParams& a, int lds_per_wave, hipStream_t st);
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather);
@@ -672,8 +674,8 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
       adj_segs.push_back(AdjSeg{adj_ent, layers[l].nx, s, l, 0});
       adj_ent += (int64_t)layers[l].nx * kAdjKI;
       adj_segs.push_back(AdjSeg{adj_ent, layers[l].ny, s, l, 1});
-      adj_ent += (int64_t)layers[l].ny * kAdjKI;
-      P->adj_maxn = std::max(P->adj_maxn, std::max(layers[l].nx, layers[l].ny));
+      adj_ent += adj_row_int2(layers[l].ny);
+      P->adj_maxn = std::max(P->adj_maxn, std::max(layers[l].nx, adj_row_ents(layers[l].ny)));
     }
   }
   P->adj_ent = adj_ent;

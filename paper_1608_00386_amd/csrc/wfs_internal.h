@@ -220,11 +220,11 @@ struct AdjParams {
   int64_t fft_adj_per_real;
 };
 
-// Table-driven gather of the layer gradient.  For a (sensor, layer, axis) whose inverse
-// stencil lists fit kAdjKI entries, entry k of layer index i is (pupil index, weight) of the
-// k-th pupil index whose forward taps touch i (increasing pupil index; pupil index -1 ends a
-// shorter list).  One segment per (sensor, layer, axis) of such layers: its first entry, its
-// layer size and who it is.
+// Table-driven gather of the layer gradient.  For a (sensor, layer) whose inverse stencil lists
+// fit kAdjKI entries, entry k of layer column i is (pupil column, weight) of the k-th pupil
+// column whose forward taps touch i (increasing; -1 ends a shorter list), and the row table
+// holds the pupil rows of each first tap row.  One segment per (sensor, layer, axis) of such
+// layers: its first entry, its layer size and who it is.
 constexpr int kAdjKI = 4;
 struct AdjSeg {
   int64_t off;
@@ -238,7 +238,7 @@ struct GatherTabParams {
   int2* tab;                 // the lists (written by the taps kernel for the call's step)
   const AdjSeg* segs;
   const int64_t* tab_off;    // [n_sensors][n_layers]: first entry of the column lists of
-                             // (s, l), the row lists follow nx * kAdjKI later; -1: not tabled
+                             // (s, l), the row tables follow nx * kAdjKI later; -1: not tabled
   int32_t blk_start[kMaxLayers + 1];  // first block of each layer within a realisation
 };
 

@@ -1,0 +1,50 @@
+"""The adjoint's table-driven gather over the pitches, grid sizes and wraps it takes."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from wfs_cases import layers_for, ngs_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(n_sa, n_sub, ratio, n, boundary, step, batch=1, theta=(0.0, 0.0)):
+    """Layer gradient against the oracle's (the bound of its other tests: the forward's float32
+    fields), twice for its bits."""
+    import torch
+    import paper_1608_00386_amd as W
+    cfg = ngs_case(n_sa, n_sub, 2 * n_sub, 2, D=0.25 * n_sa * n_sub, layers=2, n=n,
+                   pitch=0.25 / ratio, batch=batch, theta=theta)
+    for layer in cfg["layers"]:
+        layer["boundary"] = boundary
+    x = layers_for(cfg, scale=0.5)
+    g = synth.random_field((batch, oracle.n_slopes(cfg)), seed=n + step)
+    plan = W.Plan(cfg)
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    out = plan.adjoint(xt, gt, step=step).clone()
+    assert torch.equal(out, plan.adjoint(xt, gt, step=step))
+    got = out.cpu().numpy().astype(np.float64)
+    ref = oracle.adjoint(x.astype(np.float64), cfg, step, g.astype(np.float64))
+    assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
+    assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max()
+
+
+# ratio: layer pixels per pupil pixel (lists of up to four pupil columns above 2/3).  The
+# periodic grids are as small as hold the footprint in one image, so that at some step both of
+# its ends lie in the columns, and in the rows, of one wave; sizes around a wave's 64 columns
+# and 16 rows.
+@pytest.mark.parametrize("step", [0, 40, 333])
+@pytest.mark.parametrize("n_sa,n_sub,ratio,n", [
+    (8, 6, 0.68, 35), (8, 6, 0.9, 45), (8, 6, 1.0, 50), (8, 6, 1.0, 64), (8, 6, 1.3, 65),
+    (8, 6, 3.0, 145), (8, 12, 0.68, 67), (10, 10, 0.95, 97), (20, 10, 1.0, 203)])
+def test_gather_periodic(n_sa, n_sub, ratio, n, step):
+    _check(n_sa, n_sub, ratio, n, 0, step)
+
+
+@pytest.mark.parametrize("theta", [(0.0, 0.0), (60 * np.pi / 648000, -40 * np.pi / 648000)])
+@pytest.mark.parametrize("ratio,n", [(0.7, 17), (1.0, 30), (1.0, 81), (2.2, 63)])
+def test_gather_zero_boundary(ratio, n, theta):
+    """Grids smaller than the footprint, and larger, some of it beside them."""
+    _check(8, 6, ratio, n, 1, 3, batch=2, theta=theta)
