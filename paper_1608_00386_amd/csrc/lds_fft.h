@@ -89,9 +89,20 @@ __device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2&
   a3 = make_float2(d02.x - d13.y, d02.y + d13.x);  // d02 + i d13
 }
 
+// dft4 of a0, a1 and two zeros
+__device__ __forceinline__ void dft4_half(float2& a0, float2& a1, float2& a2, float2& a3) {
+  const float2 u = a0, v = a1;
+  a0 = make_float2(u.x + v.x, u.y + v.y);
+  a1 = make_float2(u.x + v.y, u.y - v.x);
+  a2 = make_float2(u.x - v.x, u.y - v.y);
+  a3 = make_float2(u.x - v.y, u.y + v.x);
+}
+
 // In-register R-point DFT, X[r] = sum_m a[m] exp(-2 pi i m r / R), natural order in and out.
-template <int R>
+// HALF (R = 16): a[8] .. a[15] are zero and are not read.
+template <int R, bool HALF = false>
 __device__ __forceinline__ void dft(float2* a) {
+  static_assert(!HALF || R == 16, "half of the inputs: radix 16");
   if constexpr (R == 2) {
     const float2 u = a[0], v = a[1];
     a[0] = make_float2(u.x + v.x, u.y + v.y);
@@ -121,9 +132,13 @@ __device__ __forceinline__ void dft(float2* a) {
     for (int m1 = 0; m1 < 4; ++m1) {
       y[m1][0] = a[m1];
       y[m1][1] = a[m1 + 4];
-      y[m1][2] = a[m1 + 8];
-      y[m1][3] = a[m1 + 12];
-      dft4(y[m1][0], y[m1][1], y[m1][2], y[m1][3]);
+      if constexpr (HALF) {
+        dft4_half(y[m1][0], y[m1][1], y[m1][2], y[m1][3]);
+      } else {
+        y[m1][2] = a[m1 + 8];
+        y[m1][3] = a[m1 + 12];
+        dft4(y[m1][0], y[m1][1], y[m1][2], y[m1][3]);
+      }
     }
     y[1][1] = rot16<1>(y[1][1]);
     y[1][2] = rot16<2>(y[1][2]);
@@ -213,6 +228,11 @@ __device__ __forceinline__ void fft_stages(float2* buf, int cnt, int ld,
     fft_stage<LOG2N, LNS, LR, POINTS, THREADS>(buf, cnt, ld, tw);
     fft_stages<LOG2N, LNS + LR, POINTS, THREADS>(buf, cnt, ld, tw);
   }
+}
+
+// log2 Ns of the last stage
+__host__ __device__ constexpr int fft_last_lns(int log2N) {
+  return log2N % 4 == 0 ? log2N - 4 : log2N / 4 * 4;
 }
 
 // In-place forward DFT, X[k] = sum_j x[j] exp(-2 pi i j k / N), of `cnt` sequences of N =

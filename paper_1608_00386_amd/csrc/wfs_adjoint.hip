@@ -23,8 +23,6 @@
 //     pupil pixels from per-step lists (one small kernel per call builds them, the gather
 //     then needs no FP64 and no searches); the others search their candidates per tile;
 //   atomic scatter: each pupil pixel adds its four weighted taps with FP32 atomics.
-#include <utility>
-
 #include "wfs_fft.h"
 #include "wfs_otf.h"
 
@@ -558,16 +556,6 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_taps_kernel(GatherTabParam
 // however the sums were organised: 64 lanes whose addresses are not strictly consecutive go
 // through the cache a quad a cycle, 16 cycles a load instead of 4.  Loading the rows as they lie
 // and picking columns from LDS, with row taps from scalar loads: 53 us.
-
-// f(0), ..., f(N - 1) as compile-time constants: the arrays they index stay in registers.
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 constexpr int kG2Cols = 2 * kWave;  // pupil columns of a window
 

@@ -15,6 +15,16 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// f(0), ..., f(N - 1) as compile-time constants: the arrays they index stay in registers.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs (block i on XCD i % 8).  Renumber so
 // that consecutive logical blocks share an XCD and therefore its L2: XCD x owns the logical
 // range [x*q + min(x, r), ...) of n = 8q + r blocks.
