@@ -698,7 +698,7 @@ def main():
     else:
         kern_ms = r1["gpu_ms_per_frame"]
         kern_name = "wfs_forward_kernel<10, gather> (per-pixel gather)"
-        traffic_key = "wfs_forward_kernel<10, 0, false, false, 2>"
+        traffic_key = "wfs_forward_kernel<10, 0, false>"
     in_wave_proj = field == "footprint" or frames == "one_launch"
     achieved = flops / (kern_ms * 1e-3)
     foot, n_phase = r1["plan"].footprint(0)

@@ -147,6 +147,7 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
   const float* rrow[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) rrow[r] = R + (int64_t)min(row0 + r, M - 1) * N;
+  const bool whole4 = (N & 3) == 0;  // (uniform) a float4 of a row is whole or past its end
   // slope slice loads: thread t stages float4 j = t & 63 of realisations t / 64 and 4 + t / 64
   auto load_s = [&](int s, auto whole, float4 (&v)[2]) {
 #pragma unroll
@@ -156,6 +157,8 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
         v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
       else if (whole)
         v[h] = ld4(S + (int64_t)b * N + k);
+      else if (whole4)
+        v[h] = k < k1 ? ld4(S + (int64_t)b * N + k) : make_float4(0.f, 0.f, 0.f, 0.f);
       else
         v[h] = ld4_below<false>(S + (int64_t)b * N, k, k1);
     }
@@ -172,6 +175,10 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
     if (whole) {
 #pragma unroll
       for (int r = 0; r < RW; ++r) v[r] = ldnt4(rrow[r] + k);
+    } else if (whole4) {
+#pragma unroll
+      for (int r = 0; r < RW; ++r)
+        v[r] = k < k1 ? ldnt4(rrow[r] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
     } else {
 #pragma unroll
       for (int r = 0; r < RW; ++r) v[r] = ld4_below<true>(rrow[r], k, k1);
@@ -183,8 +190,8 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
 #pragma unroll
     for (int b = 0; b < BB; ++b) acc[r][b] = 0.0f;
   float4 sv[2], rv[RW], rn[RW];
-  load_s(0, std::false_type{}, sv);
-  if constexpr (PF) load_r(0, std::false_type{}, rv);
+  load_s(0, k0 + 256 <= k1, sv);
+  if constexpr (PF) load_r(0, k0 + 256 <= k1, rv);
   store_s(0, sv);
   __syncthreads();
   // step s; the next slice's loads (a slice that may be short has a branch for each load)
@@ -445,11 +452,12 @@ static bool recon_aligned(const float* R, int N, const float* S) {
   return N % 4 == 0 && (uintptr_t)R % 16 == 0 && (uintptr_t)S % 16 == 0;
 }
 
-// Floats of partial sums a call wants (its split count unconstrained by the workspace), no
-// fewer than a call with a smaller B: a workspace grown by one call takes every smaller one.
-hipError_t recon_work_floats(int M, int N, int B, int64_t* floats) {
+// Floats of partial sums a call wants (its split count unconstrained by the workspace); `most`:
+// no fewer than a call with a smaller B, so that a workspace grown by one call takes every
+// smaller one.
+hipError_t recon_work_floats(int M, int N, int B, bool most, int64_t* floats) {
   *floats = 0;
-  for (int path = kReconGemv; path <= recon_path(B); ++path) {
+  for (int path = most ? kReconGemv : recon_path(B); path <= recon_path(B); ++path) {
     ReconShape sh;
     hipError_t e = recon_shape((ReconPath)path, M, B, &sh);
     if (e != hipSuccess) return e;
@@ -548,11 +556,12 @@ static std::mutex g_ws_mu;
 static std::vector<StreamWork> g_ws;       // current buffer of each (device, stream)
 static std::vector<float*> g_ws_retired;   // outgrown buffers, kept for captured graphs
 
-// The stream's buffer, grown to `floats` where it holds fewer (*have: what it holds).  While
+// The stream's buffer, grown for a call of this size and every smaller B where it holds fewer
+// than `floats` (*have: what it holds).  While
 // the stream is capturing it cannot grow: *capturing is set, *out and *have are the current
 // buffer (or null and 0).
-hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, int64_t* have,
-                             bool* capturing) {
+hipError_t recon_stream_work(hipStream_t st, int M, int N, int B, int64_t floats, float** out,
+                             int64_t* have, bool* capturing) {
   *capturing = false;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -571,6 +580,8 @@ hipError_t recon_stream_work(hipStream_t st, int64_t floats, float** out, int64_
     *capturing = true;
     return hipErrorStreamCaptureUnsupported;
   }
+  e = recon_work_floats(M, N, B, true, &floats);
+  if (e != hipSuccess) return e;
   float* p = nullptr;
   e = hipMalloc((void**)&p, sizeof(float) * (size_t)floats);
   if (e != hipSuccess) return e;
