@@ -32,6 +32,10 @@ namespace wfs {
 __host__ __device__ inline int adj_classes(int ns, int n_pix) {
   return 1 + 2 * ((ns - 1) / n_pix);
 }
+// Those kept by columns: none where the rows hold every lag already.
+__host__ __device__ inline int adj_col_classes(int ns, int n_pix) {
+  return n_pix == 1 ? 0 : adj_classes(ns, n_pix);
+}
 
 struct AdjLds {
   int ur_off, uc_off, g_off, total;
@@ -39,19 +43,20 @@ struct AdjLds {
 
 // Per-wave LDS of the adjoint: the forward layout and U on the lag classes: UR [classes][2 ns -
 // 1] (dy a multiple of n_pix, every dx) and UC (dx a multiple, every dy; zero where dy is one
-// too), then ghat along x and y.  Once the spot (or only the field) is formed, only E and the
+// too, absent for one pixel), then ghat along x and y.  Once the spot (or only the field) is formed, only E and the
 // lag-phase table of the forward layout are read again, so in the gather form (no stencil
 // taps) these go into the dead union between them when they fit; the atomic form keeps its
 // taps there and places them after the forward layout.
 __host__ __device__ inline AdjLds adj_lds_layout(int ns, int n_layers, int n_pix, bool gather) {
   const OtfLds f = otf_lds_layout(ns, n_layers, n_pix);
-  const int ub = adj_classes(ns, n_pix) * (2 * ns - 1) * 8;
+  const int rb = adj_classes(ns, n_pix) * (2 * ns - 1) * 8;
+  const int cb = adj_col_classes(ns, n_pix) * (2 * ns - 1) * 8;
   AdjLds a;
   const int e_end = (ns * ns * 8 + 15) & ~15;
-  const bool in = gather && e_end + 2 * ub + 2 * n_pix * 8 <= f.tw_off;
+  const bool in = gather && e_end + rb + cb + 2 * n_pix * 8 <= f.tw_off;
   a.ur_off = in ? e_end : f.total;
-  a.uc_off = a.ur_off + ub;
-  a.g_off = a.uc_off + ub;
+  a.uc_off = a.ur_off + rb;
+  a.g_off = a.uc_off + cb;
   a.total = in ? f.total : (a.g_off + 2 * n_pix * 8 + 15) & ~15;
   return a;
 }
@@ -119,7 +124,7 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
     const float2 k = elong_tf(sb, el, fmaf((float)dx, sb.ex, (float)dy * sb.ey), S.flux_c);
     return cmul2(cmul2(cmul2(stab[dx + NS - 1], stab[dy + NS - 1]), k), g);
   };
-  for (int t2 = lane; t2 < 2 * ncl * NL; t2 += kWave) {
+  for (int t2 = lane; t2 < (ncl + adj_col_classes(NS, np)) * NL; t2 += kWave) {
     const bool col = t2 >= ncl * NL;
     const int u = col ? t2 - ncl * NL : t2;
     const int cls = small_div<NL>(u), i = u - cls * NL;
@@ -173,7 +178,7 @@ __device__ void otf_adjoint_subap(const AdjParams& ap, int t, int64_t step, char
       }
     }
     const int c2 = c0 + z * np;
-    if (c2 < NS) {
+    if (c2 < NS && np > 1) {  // (one pixel: every lag is in UR)
       const int cls = fdiv(c2 - c + np * NS, np, S.inv_npix) - NS + hcl;
       float2 f[NS];
 #pragma unroll
@@ -760,14 +765,6 @@ static hipError_t launch_adj(AdjParams a, bool clear_grad, bool clear, hipStream
 
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather) {
   return adj_lds_layout(ns, n_layers, n_pix, gather).total;
-}
-
-// Whether wfs_adjoint takes lag-domain sensors of this size: images whose forward layout, a
-// whole lag array and three image-sized arrays fit 64 KiB per workgroup.
-bool adj_takes(int ns, int n_layers, int n_pix) {
-  const int nl = 2 * ns - 1, pitch = nl + (((1 - ns) % 16) + 16) % 16;
-  return (otf_lds_layout(ns, n_layers, n_pix).total + nl * pitch * 8 + 20 * n_pix * n_pix) *
-             kWavesPerBlock <= 65536;
 }
 
 hipError_t launch_adjoint_gather(const FwdParams& f, const float* gpsi, float* grad,

@@ -43,7 +43,6 @@ int64_t adj_row_int2(int ny);
 int fft_adj_wave_lds_bytes(int n_fft, int n_pix);
 hipError_t launch_adjoint_fft(const AdjParams& a, int lds_per_wave, hipStream_t st);
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather);
-bool adj_takes(int ns, int n_layers, int n_pix);
 hipError_t recon_work_floats(int M, int N, int B, bool most, int64_t* floats);
 hipError_t recon_stream_work(hipStream_t st, int M, int N, int B, int64_t floats, float** out,
                              int64_t* have, bool* capturing);
@@ -993,8 +992,7 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
                   G.lds_fused * kWavesPerBlock);
     }
     foot_ok = foot_ok && G.lds_foot * kWavesPerBlock <= 65536;
-    adj_ok = adj_ok && adj_takes(G.ns, n_layers, G.max_npix) &&
-             G.lds_adj * kWavesPerBlock <= 65536;
+    adj_ok = adj_ok && G.lds_adj * kWavesPerBlock <= 65536;
   }
   P->lds_foot = otf_ns ? P->groups[0].lds_foot : 0;
   P->foot_ok = otf_ns && foot_ok && foot_ent > 0 && foot_ent < (1LL << 31) / 64;

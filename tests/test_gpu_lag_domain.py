@@ -78,3 +78,26 @@ def test_adjoint_of_every_image_size_matches_the_oracle(n_sub, N, b, atomic):
         assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max()
     zero = plan.adjoint(xt, torch.zeros_like(gt), step=3)  # nothing left from the calls before
     assert not zero.any()
+
+
+# (n_sub, layers, image pixels): many layers, whose stencil taps take most of the LDS; images of
+# one pixel (every lag in a class, no column classes) and of more pixels than the field's lags
+@pytest.mark.parametrize("n_sub,layers,n_pix,atomic", [
+    (10, 31, 8, False), (12, 20, 12, False), (10, 24, 14, False), (12, 18, 1, False),
+    (12, 18, 1, True), (8, 2, 24, False), (8, 2, 24, True), (12, 4, 28, False)])
+def test_adjoint_of_many_layers_and_large_images_matches_the_oracle(n_sub, layers, n_pix, atomic):
+    import torch
+    import paper_1608_00386_amd as W
+    from wfs_cases import layers_for
+    b = next(b for b in range(1, 99) if b * n_pix >= 2 * n_sub and b * n_pix % 2 == 0)
+    cfg = lgs_case(5, n_sub, b * n_pix, b, layers=layers, n=96, pitch=0.25, n_sensors=2)
+    x = layers_for(cfg)
+    g = np.random.default_rng(3).standard_normal((1, oracle.n_slopes(cfg))).astype(np.float32)
+    plan = W.Plan(cfg, flags=W.WFS_FLAG_ADJOINT_ATOMIC if atomic else 0)
+    xt, gt = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+    ref = oracle.adjoint(x.astype(np.float64), cfg, 3, g.astype(np.float64))
+    s, a = plan.forward(xt, step=3)
+    for fwd in ({}, dict(fwd_slopes=s, fwd_aux=a)):
+        got = plan.adjoint(xt, gt, step=3, **fwd).cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
+        assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max()

@@ -1,0 +1,96 @@
+"""What the library decides on the host: the sizes it takes and what it launches, checked without
+a GPU against a recording stand-in for the HIP runtime (hip_recorder.cpp).  Each test runs in a
+process of its own, where the stand-in's symbols come before the runtime's."""
+
+import ctypes
+import importlib.util
+import os
+import shutil
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+import synth  # noqa: E402
+
+
+class Lib:
+    """libwfs.so over the recording runtime (loaded without the package, which imports torch)."""
+
+    def __init__(self, recorder):
+        self.rec = ctypes.CDLL(recorder, mode=ctypes.RTLD_GLOBAL)
+        self.rec.rec_take.restype = ctypes.c_char_p
+        spec = importlib.util.spec_from_file_location(
+            "wfs_ctypes", os.path.join(ROOT, "paper_1608_00386_amd", "_lib.py"))
+        self.t = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.t)
+        self.lib = self.t.lib()
+
+    def set(self, device=0, capturing=0, refuse_attr=0):
+        self.rec.rec_set(device, capturing, refuse_attr)
+
+    def lines(self, what):
+        """The lines of one kind since the last call: [[name, a, b], ...]."""
+        got = [ln.split() for ln in self.rec.rec_take().decode().splitlines()]
+        return [ln[1:] for ln in got if ln[0] == what]
+
+    def plan(self, cfg, flags=0):
+        ld = [self.t.layer_desc(x) for x in cfg["layers"]]
+        sd = [self.t.sensor_desc(x) for x in cfg["sensors"]]
+        h = ctypes.c_void_p()
+        rc = self.lib.wfs_plan((self.t.LayerDesc * len(ld))(*ld), len(ld), cfg["layer_stride"],
+                               (self.t.SensorDesc * len(sd))(*sd), len(sd), 1,
+                               cfg["lambda_ref_m"], cfg["dt_s"], flags, ctypes.byref(h))
+        assert rc == 0, self.lib.wfs_last_error()
+        return h
+
+    def adjoint(self, plan):
+        fake = ctypes.c_void_p(4096)  # (kernels are not run)
+        return self.lib.wfs_adjoint(plan, fake, fake, None, None, 0, fake, None)
+
+
+def _case(n_sub, layers, n_pix):
+    bin_ = next(b for b in range(1, 99) if b * n_pix >= 2 * n_sub and b * n_pix % 2 == 0)
+    return synth.small_lgs(n_sa=3, n_sub=n_sub, n_fft=n_pix * bin_, bin_=bin_, n_layers=layers,
+                           n=32, pitch=0.5)
+
+
+# (n_sub, layers, image pixels): sizes whose spot waves fit 64 KB of LDS a workgroup with room
+# for the adjoint's lag classes: many layers, the largest images, images of one pixel (every lag
+# in a class), with the stencil taps in the same LDS (atomic form) or not
+ADJOINT = [(12, 18, 12, False), (12, 24, 12, False), (12, 20, 12, False), (10, 24, 14, False),
+           (10, 30, 10, False), (10, 31, 8, False), (10, 43, 8, False), (12, 33, 9, False),
+           (4, 64, 19, False), (12, 17, 1, False), (12, 22, 1, False), (12, 17, 1, True),
+           (12, 19, 1, True), (9, 38, 1, True), (12, 18, 5, True)]
+
+
+def child_adjoint_sizes(L):
+    for n_sub, layers, n_pix, atomic in ADJOINT:
+        h = L.plan(_case(n_sub, layers, n_pix),
+                   L.t.WFS_FLAG_ADJOINT_ATOMIC if atomic else 0)
+        assert L.adjoint(h) == 0, (n_sub, layers, n_pix, atomic, L.lib.wfs_last_error())
+        assert L.lib.wfs_plan_destroy(h) == 0
+        assert not L.lines("refused")
+
+
+def _run(case, tmp_path):
+    import pytest
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    so = str(tmp_path / "hip_recorder.so")
+    src = os.path.join(ROOT, "tests", "hip_recorder.cpp")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", src, "-o", so], check=True)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), case, so],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_adjoint_takes_every_size_that_fits_its_lds(tmp_path):
+    _run("adjoint_sizes", tmp_path)
+
+
+if __name__ == "__main__":
+    globals()["child_" + sys.argv[1]](Lib(sys.argv[2]))
