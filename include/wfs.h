@@ -261,6 +261,8 @@ int wfs_project(wfs_plan_t plan, const float* layers, int64_t step, float* phase
  *   only: with them, WFS_FLAG_ADJOINT_ATOMIC returns WFS_EUNSUPPORTED.  When fwd_slopes and
  *   fwd_aux are NULL and the plan has FFT-path sensors, the noise-free forward runs first
  *   into a plan-owned buffer (allocated on the first call, with the FFT path's chunk shares).
+ *   The gather's images are cleared by the first call outside a graph capture, and by every
+ *   captured call before it (a capture mode that permits allocations may record the first).
  */
 int wfs_adjoint(wfs_plan_t plan, const float* layers, const float* grad_slopes,
                 const float* fwd_slopes, const float* fwd_aux, int64_t step,

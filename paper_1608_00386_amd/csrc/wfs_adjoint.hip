@@ -808,9 +808,7 @@ hipError_t launch_adjoint_gather_tab(const FwdParams& f, const float* gpsi, floa
 
 int adj_tab_rows() { return kG2TH; }
 
-
-// FFT-path sensors: one wave per spectrum chunk (fft_adjoint_chunk_m), after the clear of the
-// phase-gradient images and before the gather
+// FFT-path sensors: one wave per spectrum chunk (fft_adjoint_chunk_m), before the gather
 __global__ __launch_bounds__(kBlock) void wfs_adjoint_fft_kernel(AdjParams ap, int lds_per_wave) {
   extern __shared__ __align__(16) char smem[];
   const int w = threadIdx.x >> 6;

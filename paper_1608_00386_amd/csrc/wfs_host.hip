@@ -145,6 +145,7 @@ struct wfs_plan_s {
   int64_t phase_per_real = 0;
   int64_t pupil_per_real = 0;       // sum over sensors of n_pup^2
   float* d_gimg = nullptr;          // adjoint gather: [B][pupil_per_real], allocated on first use
+  bool gimg_clear = false;          // and zero outside the valid subapertures
   // device blob holding every table
   char* d_blob = nullptr;
   int64_t* d_step = nullptr;
@@ -1619,13 +1620,15 @@ int wfs_adjoint(wfs_plan_t P, const float* layers, const float* grad_slopes,
       P->d_gimg = nullptr;
       return hip_fail(ea, "wfs_adjoint: phase-gradient images");
     }
-    // pixels outside the valid subapertures are never written: zero from here on
-    ea = launch_zero(P->d_gimg, P->pupil_per_real * P->batch, (hipStream_t)stream);
-    if (ea != hipSuccess) {
-      (void)hipFree(P->d_gimg);
-      P->d_gimg = nullptr;
-      return hip_fail(ea, "wfs_adjoint: phase-gradient images");
-    }
+  }
+  if (gather && !P->gimg_clear) {
+    // pixels outside the valid subapertures are never written: zero from here on.  A clear that
+    // is recorded into a graph has not happened yet, so the next call clears as well.
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) (void)hipGetLastError();
+    hipError_t ea = launch_zero(P->d_gimg, P->pupil_per_real * P->batch, (hipStream_t)stream);
+    if (ea != hipSuccess) return hip_fail(ea, "wfs_adjoint: phase-gradient images");
+    P->gimg_clear = cs == hipStreamCaptureStatusNone;
   }
   if (fft && !P->d_adj_fwd) {  // FFT path: chunk shares and the forward outputs it needs
     hipError_t ea = hipMalloc((void**)&P->d_adj_fwd,

@@ -75,6 +75,20 @@ def child_adjoint_sizes(L):
         assert not L.lines("refused")
 
 
+def child_adjoint_clear(L):
+    """A clear recorded into a graph is no clear yet: the graph may never be launched."""
+    for warm in (False, True):  # whether an eager call comes before the capture
+        h = L.plan(_case(4, 2, 4))
+        L.lines("launch")
+        cleared = []
+        for capturing in ([0] if warm else []) + [1, 1, 0, 0, 1]:
+            L.set(capturing=capturing)
+            assert L.adjoint(h) == 0, L.lib.wfs_last_error()
+            cleared.append(sum("zero_kernel" in name for name, _, _ in L.lines("launch")))
+        assert cleared == ([1, 0, 0, 0, 0, 0] if warm else [1, 1, 1, 0, 0]), cleared
+        assert L.lib.wfs_plan_destroy(h) == 0
+
+
 def _run(case, tmp_path):
     import pytest
     cxx = shutil.which("g++") or shutil.which("c++")
@@ -90,6 +104,10 @@ def _run(case, tmp_path):
 
 def test_adjoint_takes_every_size_that_fits_its_lds(tmp_path):
     _run("adjoint_sizes", tmp_path)
+
+
+def test_adjoint_clears_its_images_outside_a_capture(tmp_path):
+    _run("adjoint_clear", tmp_path)
 
 
 if __name__ == "__main__":
