@@ -19,7 +19,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <type_traits>
 
 #include "../../include/wfs.h"
@@ -229,6 +228,21 @@ static void scr_dispatch(int log2n, F&& f) {
   }
 }
 
+// Launch with LDS bytes of dynamic LDS.  The largest sizes hold more than the default 64 KB,
+// which the current device's kernel is told before each launch: the limit belongs to one device,
+// and a process may use several.
+template <int LDS>
+static hipError_t scr_launch(void (*kernel)(ScreenParams), int blocks, int threads,
+                             const ScreenParams& p, hipStream_t st) {
+  if constexpr (LDS > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (e != hipSuccess) return e;
+  }
+  kernel<<<blocks, threads, LDS, st>>>(p);
+  return hipGetLastError();
+}
+
 extern "C" {
 
 int screen_generate(int32_t n, double pitch_m, double r0_m, double L0_m, uint64_t seed,
@@ -244,20 +258,6 @@ int screen_generate(int32_t n, double pitch_m, double r0_m, double L0_m, uint64_
     return scr_fail(WFS_EINVAL, "screen_generate: work must hold 2 n^2 floats");
   int log2n = 0;
   while ((1 << log2n) < n) ++log2n;
-  hipError_t e;
-  static std::once_flag lds_once;
-  static hipError_t lds_err = hipSuccess;
-  std::call_once(lds_once, [] {
-    for (int lg = 4; lg <= 12 && lds_err == hipSuccess; ++lg)
-      scr_dispatch(lg, [&](auto L) {  // the largest sizes hold more than the default 64 KB
-        lds_err = hipFuncSetAttribute((const void*)screen_cols_kernel<decltype(L)::value>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (lds_err == hipSuccess)
-          lds_err = hipFuncSetAttribute((const void*)screen_rows_kernel<decltype(L)::value>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      });
-  });
-  if (lds_err != hipSuccess) return scr_fail(WFS_EDEVICE, hipGetErrorString(lds_err));
   hipStream_t st = (hipStream_t)stream;
   ScreenParams p{};
   // 16-byte aligned inside the work buffer (n^2 + 2 n floats of its 2 n^2 are used)
@@ -270,19 +270,19 @@ int screen_generate(int32_t n, double pitch_m, double r0_m, double L0_m, uint64_
   p.seed_hi = (uint32_t)(seed >> 32);
   p.sid_lo = (uint32_t)stream_id;
   p.sid_hi = (uint32_t)(stream_id >> 32);
+  hipError_t e = hipSuccess;
   scr_dispatch(log2n, [&](auto L) {
-    constexpr int N = 1 << decltype(L)::value;
-    screen_rows_kernel<decltype(L)::value>
-        <<<N / 2 + 1, kScrBlock, (N + fft_span(N)) * sizeof(float2), st>>>(p);
+    constexpr int LG = decltype(L)::value, N = 1 << LG;
+    e = scr_launch<(N + fft_span(N)) * (int)sizeof(float2)>(screen_rows_kernel<LG>, N / 2 + 1,
+                                                            kScrBlock, p, st);
   });
-  if ((e = hipGetLastError()) != hipSuccess) return scr_fail(WFS_EDEVICE, hipGetErrorString(e));
+  if (e != hipSuccess) return scr_fail(WFS_EDEVICE, hipGetErrorString(e));
   scr_dispatch(log2n, [&](auto L) {
-    constexpr int N = 1 << decltype(L)::value, C = scr_cols(N);
-    screen_cols_kernel<decltype(L)::value>
-        <<<N / C, scr_col_threads(N), (N + (C / 2) * fft_pitch(N, C / 2)) * sizeof(float2), st>>>(
-            p);
+    constexpr int LG = decltype(L)::value, N = 1 << LG, C = scr_cols(N);
+    e = scr_launch<(N + (C / 2) * fft_pitch(N, C / 2)) * (int)sizeof(float2)>(
+        screen_cols_kernel<LG>, N / C, scr_col_threads(N), p, st);
   });
-  if ((e = hipGetLastError()) != hipSuccess) return scr_fail(WFS_EDEVICE, hipGetErrorString(e));
+  if (e != hipSuccess) return scr_fail(WFS_EDEVICE, hipGetErrorString(e));
   return WFS_OK;
 }
 

@@ -7,7 +7,6 @@
 // gravity stage.
 
 #include <cmath>
-#include <mutex>
 
 #include "wfs_fft.h"
 #include "wfs_otf.h"
@@ -91,18 +90,22 @@ static hipError_t launch_fft_q(const FwdParams& p, const TaskTable& t, const Cal
                        dim3((unsigned)((tasks + kWavesPerBlock - 1) / kWavesPerBlock)),
                        dim3(kBlock), fft_spot_lds(1), st, p, t, cal);
   } else {
-    // the field and the waves' tiles hold more than the default 64 KB of LDS (Q = 4)
-    static std::once_flag once;
-    static hipError_t err = hipSuccess;
-    std::call_once(once, [] {
-      err = hipFuncSetAttribute((const void*)fft_spot_kernel<Q, CAL>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, fft_spot_lds(Q));
-    });
-    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((fft_spot_kernel<Q, CAL>), dim3((unsigned)tasks),
                        dim3(fft_waves(Q) * kWave), fft_spot_lds(Q), st, p, t, cal);
   }
   return hipGetLastError();
+}
+
+// Lets the current device's kernels hold the field and the waves' tiles, more than the default
+// 64 KB of LDS at Q = 4: once per plan, on its device.
+hipError_t fft_allow_lds() {
+  static_assert(fft_spot_lds(1) <= 65536 && fft_spot_lds(2) <= 65536, "the default holds them");
+  hipError_t e = hipFuncSetAttribute((const void*)fft_spot_kernel<4, false>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, fft_spot_lds(4));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)fft_spot_kernel<4, true>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, fft_spot_lds(4));
+  return e;
 }
 
 hipError_t launch_fft_spots(const FwdParams& p, const FftTables& t, const CalibParams* cal,

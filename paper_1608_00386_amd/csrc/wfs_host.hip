@@ -21,6 +21,7 @@ hipError_t launch_forward(const FwdParams& p, int ns, const FftTables* fft, hipS
                           const SideStream* side);
 hipError_t launch_fft_spots(const FwdParams& p, const FftTables& t, const CalibParams* cal,
                             hipStream_t st);
+hipError_t fft_allow_lds();
 hipError_t launch_foot_entries(const FwdParams& p, FootEnt* out, int n_frames, hipStream_t st);
 hipError_t launch_project(const FwdParams& p, float* phase, int lds, hipStream_t st);
 int project_lds_bytes(int n_layers, int rows);
@@ -852,6 +853,9 @@ int wfs_plan(const wfs_layer_desc* layers, int32_t n_layers, int64_t layer_strid
   blob.resize((blob.size() + 255) & ~size_t(255));
 
   hipError_t e = hipGetDevice(&P->device);
+  bool fft_large = false;  // four spectrum chunks an axis
+  for (int s : fft_ids) fft_large = fft_large || sensors[s].n_fft == 4 * 32;
+  if (e == hipSuccess && fft_large) e = fft_allow_lds();
   if (e == hipSuccess) e = hipMalloc((void**)&P->d_blob, blob.size());
   if (e == hipSuccess) e = hipMemcpy(P->d_blob, blob.data(), blob.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipDeviceSynchronize();

@@ -15,7 +15,7 @@ struct Dim3 {
   uint32_t x, y, z;
 };
 
-static int g_device = 0, g_capturing = 0, g_refuse_attr = 0;
+static int g_device = 0, g_capturing = 0, g_refuse_attr = 0, g_error = 0;
 static uint64_t g_handles = 0;
 static std::map<const void*, std::string> g_names;
 static std::map<std::pair<int, const void*>, int> g_lds;  // (device, kernel): bytes allowed
@@ -76,9 +76,9 @@ int hipLaunchKernel(const void* kernel, Dim3 grid, Dim3, void**, size_t shm, voi
   log_line("launch", kernel, (long long)grid.x * grid.y * grid.z, (long long)shm);
   if (shm > 65536 && (it == g_lds.end() || (size_t)it->second < shm)) {
     log_line("refused", kernel, g_device, (long long)shm);
-    return 1;
+    g_error = 1;
   }
-  return 0;
+  return g_error;
 }
 int hipFuncSetAttribute(const void* kernel, int, int value) {
   log_line("attr", kernel, g_device, value);
@@ -118,7 +118,11 @@ int hipMemset(void* d, int v, size_t n) {
 }
 int hipDeviceSynchronize() { return 0; }
 const char* hipGetErrorString(int) { return "recorded error"; }
-int hipGetLastError() { return 0; }
+int hipGetLastError() {
+  const int e = g_error;
+  g_error = 0;
+  return e;
+}
 int hipGetSymbolAddress(void** p, const void*) {
   *p = g_symbol;
   return 0;

@@ -89,6 +89,31 @@ def child_adjoint_clear(L):
         assert L.lib.wfs_plan_destroy(h) == 0
 
 
+def child_lds_of_every_device(L):
+    """Kernels with more than 64 KB of LDS, on two devices of one process; a refused attribute is
+    an error of that call only."""
+    fake = ctypes.c_void_p(4096)
+    big = _case(4, 2, 4)
+    big["sensors"].append(synth.configs._ngs(theta_x=0.0, theta_y=0.0, n_sa=1, n_sub=40,
+                                             n_fft=128, bin_=4, lam=1.65e-6, photons=0.0,
+                                             read_noise=0.0, pupil_d=6.0, obs_d=1.0))
+
+    def screen(n):
+        return L.lib.screen_generate(n, 0.1, 0.1, 25.0, 1, 0, fake, fake, 2 * n * n, None)
+
+    for device in (0, 1, 0):
+        L.set(device=device, refuse_attr=1)
+        assert screen(4096) != 0
+        L.set(device=device)
+        for n in (1024, 2048, 4096):
+            assert screen(n) == 0, (device, n, L.lib.wfs_last_error())
+        h = L.plan(big)
+        assert L.lib.wfs_forward(h, fake, 0, 42, fake, None, None) == 0, L.lib.wfs_last_error()
+        names = L.lines("launch")
+        assert any("fft_spot_kernel" in n and int(lds) > 65536 for n, _, lds in names), names
+        assert L.lib.wfs_plan_destroy(h) == 0
+
+
 def _run(case, tmp_path):
     import pytest
     cxx = shutil.which("g++") or shutil.which("c++")
@@ -108,6 +133,10 @@ def test_adjoint_takes_every_size_that_fits_its_lds(tmp_path):
 
 def test_adjoint_clears_its_images_outside_a_capture(tmp_path):
     _run("adjoint_clear", tmp_path)
+
+
+def test_large_lds_is_allowed_on_every_device(tmp_path):
+    _run("lds_of_every_device", tmp_path)
 
 
 if __name__ == "__main__":
