@@ -55,6 +55,13 @@ __device__ __forceinline__ float4 ld4_below(const float* row, int k, int k1) {
   return v;
 }
 
+// Four products, added to a lane's sum at once: a quarter of the roundings of its growing sum
+// (one realisation of 55,608 columns: rms 5.3 -> 2.4 in 2^-24 of the root of the sum of squares,
+// for one instruction more in four).
+__device__ __forceinline__ float dot4(float4 r, float4 s) {
+  return fmaf(r.x, s.x, fmaf(r.y, s.y, fmaf(r.z, s.z, r.w * s.w)));
+}
+
 // ---------------------------------------------------------------------------------------
 // GEMV / generic: wave per (RW rows, split); lanes stride over k.
 // ---------------------------------------------------------------------------------------
@@ -86,19 +93,13 @@ __global__ __launch_bounds__(kRB) void recon_valu_kernel(const float* __restrict
       r1[r] = ldnt4(R + (int64_t)row * N + k + 256);
     }
 #pragma unroll
-    for (int r = 0; r < RW; ++r) {
-      acc[r] = fmaf(r0[r].x, s0.x, fmaf(r0[r].y, s0.y, fmaf(r0[r].z, s0.z, fmaf(r0[r].w, s0.w, acc[r]))));
-      acc[r] = fmaf(r1[r].x, s1.x, fmaf(r1[r].y, s1.y, fmaf(r1[r].z, s1.z, fmaf(r1[r].w, s1.w, acc[r]))));
-    }
+    for (int r = 0; r < RW; ++r) acc[r] += dot4(r0[r], s0) + dot4(r1[r], s1);
   }
   for (; k < kv; k += 4 * 64) {
     const float4 sv = ld4(s + k);
 #pragma unroll
-    for (int r = 0; r < RW; ++r) {
-      const int row = min(row0 + r, M - 1);
-      const float4 rv = ldnt4(R + (int64_t)row * N + k);
-      acc[r] = fmaf(rv.x, sv.x, fmaf(rv.y, sv.y, fmaf(rv.z, sv.z, fmaf(rv.w, sv.w, acc[r]))));
-    }
+    for (int r = 0; r < RW; ++r)
+      acc[r] += dot4(ldnt4(R + (int64_t)min(row0 + r, M - 1) * N + k), sv);
   }
   if (kv + lane < k1) {  // the last 1-3 columns
 #pragma unroll
@@ -207,9 +208,7 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
     for (int b = 0; b < BB; ++b) {
       const float4 x = slab[cur][b][lane];
 #pragma unroll
-      for (int r = 0; r < RW; ++r)
-        acc[r][b] = fmaf(rv[r].x, x.x, fmaf(rv[r].y, x.y,
-                    fmaf(rv[r].z, x.z, fmaf(rv[r].w, x.w, acc[r][b]))));
+      for (int r = 0; r < RW; ++r) acc[r][b] += dot4(rv[r], x);
     }
     if (next) {
       store_s(cur ^ 1, sv);
@@ -251,20 +250,32 @@ __global__ __launch_bounds__(kRB) void recon_batch_lds_kernel(const float* __res
 // instruction) and turns them into operands through its own LDS tile, the next tile's loads in
 // flight; the workgroup's four waves share the slices of the slopes, double-buffered, one
 // barrier a tile.  Loading the operands straight from memory (32 bytes a lane of 16 rows)
-// reached 3.9 TB/s of R: B = 16 at 5,400 x 55,608 took 321 us, this takes 222 us (5.4 TB/s),
+// reached 3.9 TB/s of R: B = 16 at 5,400 x 55,608 took 321 us, this takes 224 us (5.4 TB/s),
 // and up to 32 realisations read R once.  FP32 matrix instructions of 32 cycles each: 61 us of
 // the device's matrix time per 16 realisations of that size.
-// Eight accumulators a tile keep the chains of additions short.
+//
+// A matrix instruction adds its four products to the accumulator one after the other, so a chain
+// of them rounds as often as there are products.  Eight chains a tile of realisations, ended
+// after a few tiles and added to a sum, keep the error below that of one GEMV a realisation
+// (rms, in 2^-24 of the root of the sum of squares; N(0, 1) operands of 5,400 rows):
+//   columns   GEMV   eight chains a split   ended kFolds times     B    us before and after
+//   55,607    5.28   8.5                    3.3                    16   235 -> 235
+//   55,607    5.28   12.6                   4.5                    24   303 -> 318
+//   5,001     2.01   3.0                    1.50 (SHORT)           16   31.4 -> 30.7
+//   5,001     2.01   3.9                    1.92                   20   38.4 -> 42.7
+//   1,001     1.49   2.6                    1.35 (SHORT)           20   17.5 -> 18.5
+// Splits of few tiles (SHORT) end their chains twice a tile; the sum is in 64 bits there, once a
+// tile or once in two (FP64 additions take 16 cycles: every tile of 32 realisations 1.2 x).
 // ---------------------------------------------------------------------------------------
 constexpr int kTileK = 128;           // columns of one tile
 constexpr int kTileP = kTileK + 4;    // LDS pitch: 16 rows on different banks
 constexpr int kTileB = 32;            // realisations of one pass at most
+constexpr int kFolds = 8;             // times a split's chains end
 
-template <int TB>
-__global__ __launch_bounds__(kRB) void recon_mfma_kernel(const float* __restrict__ R, int M,
-                                                         int N, const float* __restrict__ S,
-                                                         int B, int chunk, int row_blocks,
-                                                         float* __restrict__ ws) {
+template <int TB, bool SHORT>
+__device__ __forceinline__ void recon_mfma(const float* __restrict__ R, int M, int N,
+                                           const float* __restrict__ S, int B, int chunk,
+                                           int row_blocks, int per_fold, float* __restrict__ ws) {
   __shared__ __align__(16) float rt[4][16][kTileP];
   __shared__ __align__(16) float sl[2][TB * 16][kTileP];
   const int sp = blockIdx.x / row_blocks, g = blockIdx.x - sp * row_blocks;
@@ -301,57 +312,120 @@ __global__ __launch_bounds__(kRB) void recon_mfma_kernel(const float* __restrict
       *reinterpret_cast<float4*>(&sl[buf][(threadIdx.x >> 5) + 8 * i][4 * (threadIdx.x & 31)]) =
           sv[i];
   };
-  v4f acc[TB][8];
+  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  v4f acc[TB][8];  // chains of products
+  typedef typename std::conditional<SHORT, double, float>::type sum_t;
+  sum_t sum[TB][4];
+  v4f even[TB];  // SHORT: the last tile of even number, where two tiles go to the sum at once
+  const bool each = TB == 1 || nt <= 5;  // (uniform) every tile does
 #pragma unroll
-  for (int t = 0; t < TB; ++t)
+  for (int tb = 0; tb < TB; ++tb) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[t][i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < 4; ++i) sum[tb][i] = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[tb][i] = zero;
+  }
+  // the chains' ends, added in pairs; the chains start again
+  auto ends = [&](int tb) {
+    v4f* c = acc[tb];
+    const v4f e = ((c[0] + c[4]) + (c[1] + c[5])) + ((c[2] + c[6]) + (c[3] + c[7]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = zero;
+    return e;
+  };
+  auto add = [&](int tb, v4f e) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[tb][i] += (sum_t)e[i];
+  };
   load_s(0);
   load_r(0);
   store_s(0);
   __syncthreads();
-  for (int t = 0; t < nt; ++t) {
-    // the wave's tile of R (its last readers are this wave's own, in order)
+  for (int t0 = 0; t0 < nt; t0 += per_fold) {
+    const int t1 = min(t0 + per_fold, nt);
+    for (int t = t0; t < t1; ++t) {
+      // the wave's tile of R (its last readers are this wave's own, in order)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      *reinterpret_cast<float4*>(&rt[wave][2 * i + lr][lc]) = rv[i];
-    wave_sync();
-    if (t + 1 < nt) {
-      load_r(t + 1);
-      load_s(t + 1);
-    }
-#pragma unroll
-    for (int q = 0; q < kTileK / 16; ++q) {
-      const float4 a = *reinterpret_cast<const float4*>(&rt[wave][i16][16 * q + 4 * kq]);
-#pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        const float4 x =
-            *reinterpret_cast<const float4*>(&sl[t & 1][tb * 16 + i16][16 * q + 4 * kq]);
-        v4f* c = acc[tb] + 4 * (q & 1);
-        c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, x.x, c[0], 0, 0, 0);
-        c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, x.y, c[1], 0, 0, 0);
-        c[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, x.z, c[2], 0, 0, 0);
-        c[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, x.w, c[3], 0, 0, 0);
+      for (int i = 0; i < 8; ++i)
+        *reinterpret_cast<float4*>(&rt[wave][2 * i + lr][lc]) = rv[i];
+      wave_sync();
+      if (t + 1 < nt) {
+        load_r(t + 1);
+        load_s(t + 1);
       }
+      v4f half[TB];
+#pragma unroll
+      for (int q = 0; q < kTileK / 16; ++q) {
+        const float4 a = *reinterpret_cast<const float4*>(&rt[wave][i16][16 * q + 4 * kq]);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+          const float4 x =
+              *reinterpret_cast<const float4*>(&sl[t & 1][tb * 16 + i16][16 * q + 4 * kq]);
+          v4f* c = acc[tb] + 4 * (q & 1);
+          c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, x.x, c[0], 0, 0, 0);
+          c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, x.y, c[1], 0, 0, 0);
+          c[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, x.z, c[2], 0, 0, 0);
+          c[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, x.w, c[3], 0, 0, 0);
+        }
+        if (SHORT && q == kTileK / 32 - 1) {
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb) half[tb] = ends(tb);
+          __builtin_amdgcn_sched_barrier(0);  // (both halves at once would spill)
+        }
+      }
+      if constexpr (SHORT) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+          const v4f e = ends(tb);
+          if (each) {
+            add(tb, half[tb]);
+            add(tb, e);
+          } else if (t & 1) {
+            add(tb, even[tb] + (half[tb] + e));
+          } else {
+            even[tb] = half[tb] + e;
+          }
+        }
+      }
+      wave_sync();
+      if (t + 1 < nt) store_s((t + 1) & 1);
+      __syncthreads();
     }
-    wave_sync();
-    if (t + 1 < nt) store_s((t + 1) & 1);
-    __syncthreads();
+    if constexpr (!SHORT) {
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb) add(tb, ends(tb));
+    }
+  }
+  if (SHORT && !each && (nt & 1)) {
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) add(tb, even[tb]);
   }
   // D[4*kq + i][i16]: row = row0 + 4 kq + i, realisation = 16 tb + i16
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
-    const v4f* c = acc[tb];
-    const v4f sum = ((c[0] + c[4]) + (c[1] + c[5])) + ((c[2] + c[6]) + (c[3] + c[7]));
     const int b = 16 * tb + i16;
     if (b < B) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = row0 + 4 * kq + i;
-        if (row < M) ws[((int64_t)sp * B + b) * M + row] = sum[i];
+        if (row < M) ws[((int64_t)sp * B + b) * M + row] = (float)sum[tb][i];
       }
     }
   }
+}
+
+template <int TB>
+__global__ __launch_bounds__(kRB) void recon_mfma_kernel(const float* R, int M, int N,
+                                                         const float* S, int B, int chunk,
+                                                         int row_blocks, int per_fold, float* ws) {
+  recon_mfma<TB, false>(R, M, N, S, B, chunk, row_blocks, per_fold, ws);
+}
+
+template <int TB>
+__global__ __launch_bounds__(kRB) __attribute__((amdgpu_waves_per_eu(TB == 1 ? 3 : 2))) void
+recon_mfma_short_kernel(const float* R, int M, int N, const float* S, int B, int chunk,
+                        int row_blocks, float* ws) {
+  recon_mfma<TB, true>(R, M, N, S, B, chunk, row_blocks, 1, ws);
 }
 
 // C[b][i] = alpha * sum_sp ws[sp][b][i] + beta * C[b][i]   (splits added in order)
@@ -362,8 +436,18 @@ __global__ __launch_bounds__(kRB) void recon_reduce_kernel(const float* __restri
   const int64_t gid = (int64_t)blockIdx.x * kRB + threadIdx.x;
   if (gid >= (int64_t)M * b_count) return;
   const int bl = (int)(gid / M), i = (int)(gid - (int64_t)bl * M);
-  float s = 0.0f;
-  for (int sp = 0; sp < splits; ++sp) s += ws[((int64_t)sp * b_count + bl) * M + i];
+  // four chains of additions, each of every fourth split
+  const float* w = ws + (int64_t)bl * M + i;
+  const int64_t step = (int64_t)b_count * M;
+  float c4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  int sp = 0;
+  for (; sp + 4 <= splits; sp += 4)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c4[k] += w[(sp + k) * step];
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (sp + k < splits) c4[k] += w[(sp + k) * step];
+  const float s = (c4[0] + c4[1]) + (c4[2] + c4[3]);
   float* c = C + (int64_t)(b_first + bl) * ldc + i;
   *c = beta == 0.0f ? alpha * s : fmaf(alpha, s, beta * *c);
 }
@@ -422,11 +506,14 @@ struct ReconShape {
   int tile_b;  // realisations of a partial-sum tile that every call of the path can run with
 };
 
-static hipError_t recon_shape(ReconPath path, int M, int B, ReconShape* sh) {
+static hipError_t recon_shape(ReconPath path, int M, int N, int B, bool aligned, ReconShape* sh) {
   sh->path = path;
   if (path == kReconBatch) {
     sh->units = ((M + kBatchRW - 1) / kBatchRW + 3) / 4 * 4;
-    sh->align = 256;
+    // (a split's last slice, if not whole, branches for each load: 8 realisations of 5,400 x
+    // 8,001 took 47 us with 64 columns, 43 with 256; few columns need the even splits: rms at
+    // 515 columns 1.45 with 256, 1.40 with 64, one GEMV a realisation 1.39)
+    sh->align = aligned || N >= 1024 ? 256 : 64;
     sh->tile_b = std::min(B, kBatchMax);
     return resident_waves(2, &sh->slots);
   }
@@ -437,7 +524,7 @@ static hipError_t recon_shape(ReconPath path, int M, int B, ReconShape* sh) {
     return resident_waves(0, &sh->slots);
   }
   sh->units = (M + 1) / 2;
-  sh->align = 256;
+  sh->align = aligned ? 256 : 64;
   sh->tile_b = 1;
   return resident_waves(1, &sh->slots);
 }
@@ -453,18 +540,21 @@ static bool recon_aligned(const float* R, int N, const float* S) {
 }
 
 // Floats of partial sums a call wants (its split count unconstrained by the workspace); `most`:
-// no fewer than a call with a smaller B, so that a workspace grown by one call takes every
-// smaller one.
-hipError_t recon_work_floats(int M, int N, int B, bool most, int64_t* floats) {
+// no fewer than a call with a smaller B or the other alignment, so that a workspace grown by one
+// call takes them all.
+hipError_t recon_work_floats(const float* R, int M, int N, const float* S, int B, bool most,
+                             int64_t* floats) {
   *floats = 0;
-  for (int path = most ? kReconGemv : recon_path(B); path <= recon_path(B); ++path) {
-    ReconShape sh;
-    hipError_t e = recon_shape((ReconPath)path, M, B, &sh);
-    if (e != hipSuccess) return e;
-    int chunk;
-    const int splits = choose_splits(sh.units, N, sh.align, sh.slots, INT32_MAX, &chunk);
-    *floats = std::max(*floats, (int64_t)splits * sh.tile_b * M);
-  }
+  const bool aligned = recon_aligned(R, N, S);
+  for (int path = most ? kReconGemv : recon_path(B); path <= recon_path(B); ++path)
+    for (int other = 0; other <= (most ? 1 : 0); ++other) {
+      ReconShape sh;
+      hipError_t e = recon_shape((ReconPath)path, M, N, B, aligned != (other != 0), &sh);
+      if (e != hipSuccess) return e;
+      int chunk;
+      const int splits = choose_splits(sh.units, N, sh.align, sh.slots, INT32_MAX, &chunk);
+      *floats = std::max(*floats, (int64_t)splits * sh.tile_b * M);
+    }
   return hipSuccess;
 }
 
@@ -483,8 +573,9 @@ hipError_t recon_launch(const float* R, int M, int N, const float* S, int B, flo
                         hipStream_t st) {
   ReconPath path = recon_path(B);
   if (path != kReconGemv && ws_floats < (int64_t)std::min(B, 16) * M) path = kReconGemv;
+  const bool aligned = recon_aligned(R, N, S);
   ReconShape sh;
-  hipError_t e = recon_shape(path, M, B, &sh);
+  hipError_t e = recon_shape(path, M, N, B, aligned, &sh);
   if (e != hipSuccess) return e;
   if (ws_floats < M) return hipErrorInvalidValue;
   int chunk;
@@ -515,12 +606,24 @@ hipError_t recon_launch(const float* R, int M, int N, const float* S, int B, flo
       const int splits = choose_splits(sh.units, N, sh.align, bc > 16 ? sh.slots / 2 : sh.slots,
                                        ws_floats / ((int64_t)bc * M), &chunk);
       const int grid = sh.units / 4 * splits;
-      if (bc <= 16)
-        hipLaunchKernelGGL(recon_mfma_kernel<1>, dim3(grid), dim3(kRB), 0, st, R, M, N,
-                           S + (int64_t)b0 * N, bc, chunk, sh.units / 4, ws);
-      else
-        hipLaunchKernelGGL(recon_mfma_kernel<2>, dim3(grid), dim3(kRB), 0, st, R, M, N,
-                           S + (int64_t)b0 * N, bc, chunk, sh.units / 4, ws);
+      // Chains ended kFolds times; with more than 16 realisations and rows of whole float4s
+      // twice (rms 8.9 at 55,608 columns, 313 us for 32 realisations; once 12.6 and 308, kFolds
+      // times 4.5 and 326), where nothing asks for a GEMV's exactness.  SHORT up to kFolds tiles:
+      // from there on chains of one or more tiles are as exact as a GEMV's and take less (16
+      // tiles, 5,400 x 8,001 and 20 realisations: rms 2.2 and 60.5 us, SHORT 1.6 and 63.7, a
+      // GEMV 2.3).
+      const bool exact = bc <= 16 || !aligned;
+      const float* sb = S + (int64_t)b0 * N;
+      const int tiles = chunk / kTileK;
+      if (exact && tiles <= kFolds) {
+        const auto k = bc <= 16 ? recon_mfma_short_kernel<1> : recon_mfma_short_kernel<2>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(kRB), 0, st, R, M, N, sb, bc, chunk, sh.units / 4,
+                           ws);
+      } else {
+        const auto k = bc <= 16 ? recon_mfma_kernel<1> : recon_mfma_kernel<2>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(kRB), 0, st, R, M, N, sb, bc, chunk, sh.units / 4,
+                           exact ? tiles / kFolds : (tiles + 1) / 2, ws);
+      }
       e = hipGetLastError();
       if (e == hipSuccess) e = recon_reduce(ws, M, bc, splits, C, ldc, alpha, beta, b0, st);
       if (e != hipSuccess) return e;
@@ -560,8 +663,8 @@ static std::vector<float*> g_ws_retired;   // outgrown buffers, kept for capture
 // than `floats` (*have: what it holds).  While
 // the stream is capturing it cannot grow: *capturing is set, *out and *have are the current
 // buffer (or null and 0).
-hipError_t recon_stream_work(hipStream_t st, int M, int N, int B, int64_t floats, float** out,
-                             int64_t* have, bool* capturing) {
+hipError_t recon_stream_work(hipStream_t st, const float* R, int M, int N, const float* S, int B,
+                             int64_t floats, float** out, int64_t* have, bool* capturing) {
   *capturing = false;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -580,7 +683,7 @@ hipError_t recon_stream_work(hipStream_t st, int M, int N, int B, int64_t floats
     *capturing = true;
     return hipErrorStreamCaptureUnsupported;
   }
-  e = recon_work_floats(M, N, B, true, &floats);
+  e = recon_work_floats(R, M, N, S, B, true, &floats);
   if (e != hipSuccess) return e;
   float* p = nullptr;
   e = hipMalloc((void**)&p, sizeof(float) * (size_t)floats);

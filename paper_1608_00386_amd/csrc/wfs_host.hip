@@ -44,9 +44,10 @@ int64_t adj_row_int2(int ny);
 int fft_adj_wave_lds_bytes(int n_fft, int n_pix);
 hipError_t launch_adjoint_fft(const AdjParams& a, int lds_per_wave, hipStream_t st);
 int adj_lds_bytes(int ns, int n_layers, int n_pix, bool gather);
-hipError_t recon_work_floats(int M, int N, int B, bool most, int64_t* floats);
-hipError_t recon_stream_work(hipStream_t st, int M, int N, int B, int64_t floats, float** out,
-                             int64_t* have, bool* capturing);
+hipError_t recon_work_floats(const float* R, int M, int N, const float* S, int B, bool most,
+                             int64_t* floats);
+hipError_t recon_stream_work(hipStream_t st, const float* R, int M, int N, const float* S, int B,
+                             int64_t floats, float** out, int64_t* have, bool* capturing);
 int64_t recon_static_work_floats();
 int64_t recon_min_work_floats(const float* R, int M, int N, const float* S, int B);
 hipError_t recon_static_work(float** out);
@@ -1866,15 +1867,15 @@ int recon_apply(const float* R, int32_t M, int32_t N, const float* S, int32_t B,
     return fail(WFS_EINVAL, "recon_apply: non-finite alpha or beta");
   hipStream_t st = (hipStream_t)stream;
   int64_t floats = 0, have = 0;
-  hipError_t e = recon_work_floats(M, N, B, false, &floats);
+  hipError_t e = recon_work_floats(R, M, N, S, B, false, &floats);
   if (e != hipSuccess) return hip_fail(e, "recon_apply");
   float* ws = nullptr;
   bool capturing = false;
-  e = recon_stream_work(st, M, N, B, floats, &ws, &have, &capturing);
+  e = recon_stream_work(st, R, M, N, S, B, floats, &ws, &have, &capturing);
   if (capturing) {
     // operands that are not 16-byte aligned are taken with a single realisation's workspace
     if (recon_min_work_floats(R, M, N, S, B) == M) {
-      e = recon_work_floats(M, N, 1, false, &floats);
+      e = recon_work_floats(R, M, N, S, 1, false, &floats);
       if (e != hipSuccess) return hip_fail(e, "recon_apply");
     }
     if (!ws || have < floats)

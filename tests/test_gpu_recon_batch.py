@@ -47,3 +47,35 @@ def test_recon_noalloc_many_rows(M, B):
     """More rows than the fixed array holds tiles of 16 (one realisation a pass; unaligned rows
     only) or of 32 realisations."""
     _check(M, 3, 1, B, True)
+
+
+@pytest.mark.parametrize("M,N,Bs", [
+    (5400, 55607, (8, 16, 24)), (5400, 55608, (16,)), (5400, 8001, (8, 20)),
+    (3000, 1001, (2, 9, 16, 24)), (3000, 515, (8, 16, 20)), (64, 20001, (8, 12, 32))])
+def test_recon_sums_are_as_exact_as_a_gemv(M, N, Bs):
+    """The rms error over all sums is within that of a GEMV per realisation: 64 lanes add every
+    64th product of a split one after the other, (L + 1) / 2 roundings of the variance of all N
+    products for chains of L, then a tree of 6 levels and the splits in order, half a rounding
+    each.  The splits: as many as 8,192 waves of two rows hold, of at least 256 columns, whole
+    groups of 64.  A rounding is at most 2^-24 of its value, uniformly distributed (1 / 3)."""
+    import torch
+    import paper_1608_00386_amd as W
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    R = torch.randn(M, N, device="cuda", generator=gen)
+    S = torch.randn(max(Bs), N, device="cuda", generator=gen)
+    ref = torch.empty(max(Bs), M, dtype=torch.float64, device="cuda")
+    rss = torch.empty_like(ref)
+    for i in range(0, M, 600):
+        r = R[i:i + 600].double()
+        ref[:, i:i + 600] = S.double() @ r.T
+        rss[:, i:i + 600] = ((S.double() ** 2) @ (r ** 2).T).sqrt()
+    splits = max(1, min(8192 // ((M + 1) // 2), N // 256))
+    chunk = -(-(-(-N // splits)) // 64) * 64
+    splits = -(-N // chunk)
+    bound = 2.0 ** -24 * (((chunk / 64 + 1) / 2 + 6 + splits / 2) / 3) ** 0.5
+    for B in Bs:
+        for noalloc in (False, True):
+            C = torch.empty(B, M, device="cuda")
+            W.recon_apply(R, S[:B], C, noalloc=noalloc)
+            rms = float(((C.double() - ref[:B]) / rss[:B]).square().mean().sqrt())
+            assert rms <= bound, (B, noalloc, rms / bound)
