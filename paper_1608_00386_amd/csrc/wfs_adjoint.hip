@@ -237,7 +237,8 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_kernel(AdjParams ap) {
 constexpr int kGTW = 64;
 constexpr int kGPix = 4;
 constexpr int kGTH = kGPix * kBlock / kGTW;
-constexpr int kGCols = 128;  // candidate pupil columns per pass
+constexpr int kGCols = 128;  // candidate pupil columns per pass, the last one zero
+constexpr int kGPass = kGCols - 1;
 constexpr int kGRows = 32;   // candidate pupil rows per pass
 
 // Candidate taps of a tile: pupil index k, the tap's lower index relative to the tile start
@@ -292,7 +293,7 @@ __device__ __forceinline__ void image_range(double a, double b, int n, double in
 
 // Layer gradient, gather form: block = (realisation, layer, kGTH x kGTW tile); thread =
 // layer pixel.  For every sensor, pass by pass over the tile's candidate pupil rows and
-// columns (every periodic image, kGRows x kGCols at a time): their exact forward taps and the
+// columns (every periodic image, kGRows x kGPass at a time): their exact forward taps and the
 // rectangle of the sensor's phase-gradient image they span go to LDS (one batch of coalesced
 // loads); then each wave (one layer row) walks the candidate rows, and each lane the few
 // candidate columns whose taps reach its pixel, summing weight x gradient in a fixed order.
@@ -343,8 +344,8 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_kernel(GatherParams
           int c_lo, c_hi;
           cand_range(A.inv_ax, bx, (double)xshift, (double)(xshift + kGTW - 1), npup, c_lo,
                      c_hi);
-          for (int c0 = c_lo; c0 <= c_hi; c0 += kGCols) {
-            const int nc = min(kGCols, c_hi - c0 + 1);
+          for (int c0 = c_lo; c0 <= c_hi; c0 += kGPass) {
+            const int nc = min(kGPass, c_hi - c0 + 1);
             __syncthreads();  // previous pass done with the tables
             if (tid < nr) rt[tid] = gather_tap(A.ay, A.by0, A.dby, stepd, r0 + tid, yshift);
             if (tid < nc) ct[tid] = gather_tap(A.ax, A.bx0, A.dbx, stepd, c0 + tid, xshift);
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_kernel(GatherParams
             bool more = false;
 #pragma unroll
             for (int k = 0; k < kGC4; ++k) {
-              qk[k] = 0;
+              qk[k] = kGPass;  // (past the run: zero; a column beside it may hold an infinity)
               wk[k] = 0.0f;
               const int qc = q0 + k;
               if (qc < nc && ct[qc].rel <= lx) {
@@ -568,10 +569,11 @@ constexpr int kG2Cols = 2 * kWave;  // pupil columns of a window
 // (window positions lane and lane + 64).  Its first tap rows -1 .. kG2R - 1 go by in pairs, the
 // pupil rows of the next pair in flight while one is summed into the layer rows (over the
 // window's columns), their entries a pair further ahead.  Every four finished layer rows pass
-// through LDS, where a lane reads its NC columns from position at.
+// through LDS, where a lane reads its NC columns from their positions.
 template <int NC>
 __device__ __forceinline__ void gather_rows(const float* gs, const RowEnt* ents,
-                                            const uint32_t (&col)[2], int lane, int at,
+                                            const uint32_t (&col)[2], int lane,
+                                            const int (&at)[kAdjKI],
                                             const float (&wc)[kAdjKI], float4* buf,
                                             float (&acc)[kG2R]) {
   constexpr int CH = 2, NG = (kG2R + CH) / CH;
@@ -619,7 +621,7 @@ __device__ __forceinline__ void gather_rows(const float* gs, const RowEnt* ents,
           buf[lane + kWave] = make_float4(r[row - 3][1], r[row - 2][1], r[row - 1][1], r[row][1]);
           wave_sync();
           float4 x[NC];
-          static_for<NC>([&](auto q) __attribute__((always_inline)) { x[q] = buf[at + q]; });
+          static_for<NC>([&](auto q) __attribute__((always_inline)) { x[q] = buf[at[q]]; });
           static_for<NC>([&](auto q) __attribute__((always_inline)) {
             acc[row - 4] = fmaf(wc[q], x[q].x, acc[row - 4]);
             acc[row - 3] = fmaf(wc[q], x[q].y, acc[row - 3]);
@@ -635,7 +637,7 @@ __device__ __forceinline__ void gather_rows(const float* gs, const RowEnt* ents,
 }
 
 __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTabParams g) {
-  __shared__ float4 buf_s[kWavesPerBlock][kG2Cols + kAdjKI];  // (the last: zero)
+  __shared__ float4 buf_s[kWavesPerBlock][kG2Cols + 1];  // (the last: zero)
   const FwdParams& p = g.f;
   const int nl = p.n_layers;
   const int per_real = g.blk_start[nl];
@@ -655,7 +657,7 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTa
   if (nrows <= 0) return;                  // no block-wide barrier below
   const bool xin = x < L.nx;
   float4* buf = buf_s[wave];
-  if (lane < kAdjKI) buf[kG2Cols + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (lane == 0) buf[kG2Cols] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   float acc[kG2R];
   static_for<kG2R>([&](auto yy) __attribute__((always_inline)) { acc[yy] = 0.0f; });
   const float* gb = g.gpsi + (int64_t)b * p.pupil_per_real;
@@ -703,7 +705,9 @@ __global__ __launch_bounds__(kBlock) void wfs_adjoint_gather_tab_kernel(GatherTa
       const int c0 = __builtin_amdgcn_readlane(cf, __builtin_ctzll(left));
       const bool part = ((left >> lane) & 1) && cf >= c0 && cf + ncol <= c0 + kG2Cols;
       left &= ~__builtin_amdgcn_ballot_w64(part);
-      const int at = part ? cf - c0 : kG2Cols;
+      int at[kAdjKI];  // past the lane's list: zero (a column beside it may hold an infinity)
+#pragma unroll
+      for (int k = 0; k < kAdjKI; ++k) at[k] = part && wc[k] != 0.0f ? cf - c0 + k : kG2Cols;
       const uint32_t col[2] = {(uint32_t)min(c0 + lane, npup_s - 1),
                                (uint32_t)min(c0 + kWave + lane, npup_s - 1)};
       if (ncol == 1)

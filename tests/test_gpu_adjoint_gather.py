@@ -48,3 +48,29 @@ def test_gather_periodic(n_sa, n_sub, ratio, n, step):
 def test_gather_zero_boundary(ratio, n, theta):
     """Grids smaller than the footprint, and larger, some of it beside them."""
     _check(8, 6, ratio, n, 1, 3, batch=2, theta=theta)
+
+
+@pytest.mark.parametrize("boundary", [0, 1])
+@pytest.mark.parametrize("ratio", [0.3, 0.68, 0.8, 1.2])
+@pytest.mark.parametrize("sub", [10, 20])
+def test_gather_of_an_infinite_gradient_stays_in_its_stencils(ratio, boundary, sub):
+    """One subaperture's slope gradient is infinite (one at the pupil's left edge, or inside): the
+    layer pixels that are not finite are those of its own stencils.  (Lists of other lengths in
+    a wave's columns; no layer row or column falls on a pupil pixel, and none lies off the
+    grids, where a stencil has a weight of zero.)"""
+    import torch
+    import paper_1608_00386_amd as W
+    cfg = ngs_case(8, 6, 12, 2, D=12.0, layers=2, n=64, pitch=0.25 / ratio, wind=False,
+                   theta=(0.37e-5, -0.73e-5))
+    for layer in cfg["layers"]:
+        layer["boundary"] = boundary
+        layer["alt_m"] += 1000.0
+    x = layers_for(cfg, scale=0.5)
+    g = synth.random_field((1, oracle.n_slopes(cfg)), seed=7)
+    g[0, sub] = np.inf
+    got = W.Plan(cfg).adjoint(torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda(), step=0)
+    with np.errstate(invalid="ignore"):
+        ref = oracle.adjoint(x.astype(np.float64), cfg, 0, g.astype(np.float64))
+    bad = ~np.isfinite(ref)
+    assert 0 < bad.sum() < bad.size / 4
+    assert np.array_equal(~np.isfinite(got.cpu().numpy()), bad)
