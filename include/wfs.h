@@ -358,7 +358,8 @@ int wfs_calibrate(wfs_plan_t plan, const float* base, int64_t act_offset, int32_
  *   A exp(i (lambda_ref/lambda) phi) is zero-padded to n_fft[l] x n_fft[l] (a power of two in
  *   [max(16, n_pup), 4096]; PSF pixel = lambda / (n_fft dx) rad).  Layers as in wfs_plan
  *   (offsets inside layer_stride, periodic or zero boundary, frozen flow at t = step dt_s).
- *   Allocates the plan's device tables and a [n_stars][n_pup][max n_fft] complex work buffer.
+ *   Allocates the plan's device tables, a [n_stars][n_pup][max n_fft] complex work buffer and
+ *   [n_stars][n_pup][n_pup] floats for the phase.
  * psf_plan_info -- floats of the PSF buffer (sum over l of n_stars n_fft[l]^2), the first float
  *   of each wavelength's images (psf_offsets[n_lambda]), and the lit pupil pixels.  Any output
  *   may be NULL.

@@ -72,7 +72,7 @@ struct PsfParams {
 // Few waves (less than two a SIMD) wait for memory layer after layer: two rows a wave then,
 // and the rows of D = 5 layers on their way at once (one star of 150 pixels, 13 layers: 16.5 us
 // with eight rows a wave, 11.5 so).  Many waves hide it and read less with eight rows (nine
-// stars of 800 pixels: 58 us, with four rows 73 us).
+// stars of 800 pixels and 13 layers: 61 us, with four rows 71 us).
 constexpr int kPhaseWaves = kPsfBlock / 64;
 constexpr int phase_rows(bool few) { return few ? 2 : 8; }
 // column taps, row taps of a layer
@@ -109,8 +109,8 @@ psf_phase_kernel(PsfParams p) {
   PhaseRows* rows = reinterpret_cast<PhaseRows*>(taps + p.n_layers * NT);
   const int tid = threadIdx.x, n = p.n_pup, nl = p.n_layers;
   // the stars of a tile one after the other on one XCD, neighbouring tiles too: they read
-  // mostly the same layer pixels (in star-major order the layers came from memory 7 times
-  // as often: 68 us, so 51)
+  // mostly the same layer pixels (stars in order of launch 74 us, star after star on each XCD
+  // 65, tiles in order of launch 63, so 61)
   const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
   const int s = lb % p.n_stars, tile = lb / p.n_stars, strips = (n + 63) / 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -318,7 +318,7 @@ __host__ __device__ constexpr int psf_row_pitch(int N) { return fft_span(N) + (N
 // Bound by issue and by the 118 MB of T.  One kernel a pupil row that formed the phase too,
 // column taps again for every row, with half of its threads idle in the radix-16 stages, took
 // 137 us a frame (nine stars of 800 pupil pixels, 13 layers, N = 2,048); the phase takes
-// 58 us and this pass 46 us.  Few columns (less than two workgroups a CU) run one a
+// 61 us and this pass 43 us.  Few columns (less than two workgroups a CU) run one a
 // workgroup.
 template <int LOG2N, int RY, bool HALF>
 __global__ __launch_bounds__(psf_row_threads(LOG2N, RY)) void psf_rows_kernel(PsfParams p) {
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(psf_row_threads(LOG2N, RY)) void psf_rows_kernel(Ps
 // last one adds to the image straight from registers, its old values loaded before the stages.
 // With a workgroup per group that staged points and results in LDS, load, transform and update
 // one after the other, and 32-byte pieces of image rows (x transformed first), nine stars of
-// 800 pupil pixels at N = 2,048 took 185 us a frame, 86 us so (118 MB of T and 302 MB of image
+// 800 pupil pixels at N = 2,048 took 185 us a frame, 80 us so (118 MB of T and 302 MB of image
 // a frame).
 constexpr int kPsfColBlock = 1024;
 

@@ -13,7 +13,7 @@
 
 namespace wfs {
 
-// Register budget of the lag-domain kernels (waves per SIMD): the split field's LDS (4.4 KB
+// Register budget of the lag-domain kernels (waves per SIMD): the split field's LDS (4.7 KB
 // per wave at n_sub = 10) lets 8 four-wave blocks share a CU, the staged footprint's 5.
 template <int FIELD, bool PROJ>
 constexpr int otf_waves_per_simd() {

@@ -1991,7 +1991,9 @@ static bool calib_sparse(wfs_plan_t P, int64_t act_offset, int32_t n_act, CalibC
 // The interaction-matrix rows: the unpoked entries everywhere, then the reached subapertures of
 // every actuator in one launch per lag-domain group, and the FFT-path sensors (which read
 // projected phase) a chunk of batch / 2 actuators at a time on the plan's second stream.
-// ws holds the unpoked slopes of one realisation; the FFT-path chunks write behind them.
+// ws holds the unpoked slopes of realisation 0, and the chunks of the second stream write over
+// them: whatever reads them (the fill here, the caller's reference slopes) is queued on st before
+// the fork.
 static hipError_t calibrate_sparse(wfs_plan_t P, const float* layers, int64_t act_offset,
                                    int32_t n_act, float amp, int64_t step, float* im,
                                    int64_t ld_im, float* ws, float* wa, const CalibCells& cells,

@@ -159,7 +159,9 @@ class Plan:
         """dict(field, frames, xcd_remap, fft_launch, proj_rows) of the current launch
         schedule: field is where a frame's spot waves get the phase ("gather", "split",
         "footprint"), frames how ``forward_steps`` runs ("sequential", "pipelined",
-        "one_launch", "overlapped": the next frame projected on a second stream), fft_launch where FFT-path blocks run ("side_stream" or "same_launch"),
+        "one_launch", "overlapped": the next frame projected on a second stream), fft_launch
+        where the FFT-path sensors' launch goes ("side_stream": beside the lag-domain launch;
+        "same_launch": before it on the caller's stream),
         proj_rows the projection kernel's pupil rows per block, lag_passes the value last set
         (2 or 3; no kernel depends on it)."""
         v = [ctypes.c_int32() for _ in range(6)]
