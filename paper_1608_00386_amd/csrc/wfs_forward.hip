@@ -134,11 +134,10 @@ hipError_t launch_forward(const FwdParams& p, int ns, const FftTables* fft, hipS
   }
   e = hipEventRecord(side->fork, st);
   if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
-  if (e == hipSuccess) e = launch_fft_spots(p, *fft, nullptr, side->stream);
+  if (e != hipSuccess) return e;
+  e = launch_fft_spots(p, *fft, nullptr, side->stream);
   if (e == hipSuccess) e = launch_forward_ns(p, ns, st);
-  if (e == hipSuccess) e = hipEventRecord(side->join, side->stream);
-  if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join, 0);
-  return e;
+  return join_stream(st, side->stream, side->join, e);
 }
 
 int foot_pitch(int ns) { return (ns + 2) | 1; }

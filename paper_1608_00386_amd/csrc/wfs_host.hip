@@ -1334,6 +1334,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
     if (fs != st) {
       e = hipEventRecord(P->side.fork, st);
       if (e == hipSuccess) e = hipStreamWaitEvent(fs, P->side.fork, 0);
+      if (e != hipSuccess) return e;
     }
     for (int k = 0; k < n && e == hipSuccess; ++k) {
       FwdParams a = frame(k);
@@ -1344,11 +1345,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       e = launch_fft_spots(a, P->fft_tab, nullptr, fs);
     }
     if (e == hipSuccess) e = foot_frames();
-    if (e == hipSuccess && fs != st) {
-      e = hipEventRecord(P->side.join, fs);
-      if (e == hipSuccess) e = hipStreamWaitEvent(st, P->side.join, 0);
-    }
-    return e;
+    return fs != st ? join_stream(st, fs, P->side.join, e) : e;
   }
   if (frames == 3 && P->ovl.stream && P->d_phase) {
     float* buf[2] = {P->d_phase, P->d_phase2};
@@ -1380,7 +1377,7 @@ static hipError_t run_steps(wfs_plan_t P, const float* layers, int64_t step0, in
       if (e == hipSuccess) e = hipEventRecord(P->ovl.spot_done[k & 1], st);
     }
     // the last projection is joined by the wait before the last spot launch
-    return e;
+    return e == hipSuccess ? e : join_stream(st, ps, P->ovl.fork, e);
   }
   if (!pipelined) {
     for (int k = 0; k < n && e == hipSuccess; ++k) e = launch_fwd_modes(P, frame(k), st);
@@ -2026,9 +2023,8 @@ static hipError_t calibrate_sparse(wfs_plan_t P, const float* layers, int64_t ac
       a.batch = 2 * c.n_act;
       e = calib_fft(a, P->fft_tab, c, P->d_phase, P->proj_lds_fft, fs);
     }
-    if (e != hipSuccess) return e;
   }
-  e = launch_foot_entries(p, P->d_foot_ent, 1, st);
+  if (e == hipSuccess) e = launch_foot_entries(p, P->d_foot_ent, 1, st);
   for (size_t g = 0; g < P->groups.size() && e == hipSuccess; ++g) {
     const OtfGroup& G = P->groups[g];
     FwdParams a = p;
@@ -2039,11 +2035,7 @@ static hipError_t calibrate_sparse(wfs_plan_t P, const float* layers, int64_t ac
     q.per_act = q.cells * (int32_t)G.ids.size();
     if (q.per_act > 0) e = calib_spots(a, G.ns, q, st);
   }
-  if (e == hipSuccess && fs != st) {
-    e = hipEventRecord(P->side.join, fs);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, P->side.join, 0);
-  }
-  return e;
+  return fs != st ? join_stream(st, fs, P->side.join, e) : e;
 }
 
 int wfs_calibrate(wfs_plan_t P, const float* base, int64_t act_offset, int32_t n_act,

@@ -197,6 +197,14 @@ struct SideStream {
   hipEvent_t fork = nullptr, join = nullptr;
 };
 
+// What is queued on st from here on waits for what `from` holds, also where `e` says that a
+// launch failed in between: the caller may free its buffers then.  Returns e, or the join's error.
+inline hipError_t join_stream(hipStream_t st, hipStream_t from, hipEvent_t event, hipError_t e) {
+  hipError_t j = hipEventRecord(event, from);
+  if (j == hipSuccess) j = hipStreamWaitEvent(st, event, 0);
+  return e == hipSuccess ? j : e;
+}
+
 // Sparse calibration (noise-free sensors, actuators of zero-boundary grids): only the
 // subapertures whose stencils can touch a poked element are formed.
 struct CalibParams {

@@ -16,6 +16,7 @@ struct Dim3 {
 };
 
 static int g_device = 0, g_capturing = 0, g_refuse_attr = 0, g_error = 0;
+static int g_fail_launch = -1;  // launches until one fails (-1: none does)
 static uint64_t g_handles = 0;
 static std::map<const void*, std::string> g_names;
 static std::map<std::pair<int, const void*>, int> g_lds;  // (device, kernel): bytes allowed
@@ -36,13 +37,15 @@ static void log_line(const char* what, const void* kernel, long long a, long lon
 extern "C" {
 
 // Test side: the current device, whether streams are capturing, whether attributes are refused,
-// and the lines written since the last call ("launch name blocks lds" / "malloc - bytes 0" /
-// "attr name device bytes").
+// the launch that fails (counted from 0; -1: none), and the lines written since the last call
+// ("launch name blocks lds" / "malloc - bytes 0" / "attr name device bytes", and the order of
+// streams: "on - stream 0" for a launch, "record - stream event", "wait - stream event").
 void rec_set(int device, int capturing, int refuse_attr) {
   g_device = device;
   g_capturing = capturing;
   g_refuse_attr = refuse_attr;
 }
+void rec_fail_launch(int n) { g_fail_launch = n; }
 const char* rec_take() {
   static std::string out;
   out.swap(g_log);
@@ -71,7 +74,9 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shm, void** strea
   *stream = g_stream;
   return 0;
 }
-int hipLaunchKernel(const void* kernel, Dim3 grid, Dim3, void**, size_t shm, void*) {
+int hipLaunchKernel(const void* kernel, Dim3 grid, Dim3, void**, size_t shm, void* stream) {
+  if (g_fail_launch >= 0 && g_fail_launch-- == 0) return g_error = 1;
+  log_line("on", nullptr, (long long)stream, 0);
   const auto it = g_lds.find({g_device, kernel});
   log_line("launch", kernel, (long long)grid.x * grid.y * grid.z, (long long)shm);
   if (shm > 65536 && (it == g_lds.end() || (size_t)it->second < shm)) {
@@ -133,7 +138,10 @@ int hipEventCreate(void** e) {
 }
 int hipEventCreateWithFlags(void** e, unsigned) { return hipEventCreate(e); }
 int hipEventDestroy(void*) { return 0; }
-int hipEventRecord(void*, void*) { return 0; }
+int hipEventRecord(void* event, void* stream) {
+  log_line("record", nullptr, (long long)stream, (long long)event);
+  return 0;
+}
 int hipEventSynchronize(void*) { return 0; }
 int hipEventElapsedTime(float* ms, void*, void*) {
   *ms = 1.0f;
@@ -145,6 +153,9 @@ int hipStreamIsCapturing(void*, int* status) {
   *status = g_capturing;
   return 0;
 }
-int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
+int hipStreamWaitEvent(void* stream, void* event, unsigned) {
+  log_line("wait", nullptr, (long long)stream, (long long)event);
+  return 0;
+}
 
 }  // extern "C"

@@ -36,12 +36,18 @@ class Lib:
         got = [ln.split() for ln in self.rec.rec_take().decode().splitlines()]
         return [ln[1:] for ln in got if ln[0] == what]
 
-    def plan(self, cfg, flags=0):
+    def ops(self):
+        """Launches, event records and waits since the last call, in order."""
+        got = [ln.split() for ln in self.rec.rec_take().decode().splitlines()]
+        return [(ln[0], ln[1], int(ln[2]), int(ln[3])) for ln in got
+                if ln[0] in ("on", "record", "wait")]
+
+    def plan(self, cfg, flags=0, batch=1):
         ld = [self.t.layer_desc(x) for x in cfg["layers"]]
         sd = [self.t.sensor_desc(x) for x in cfg["sensors"]]
         h = ctypes.c_void_p()
         rc = self.lib.wfs_plan((self.t.LayerDesc * len(ld))(*ld), len(ld), cfg["layer_stride"],
-                               (self.t.SensorDesc * len(sd))(*sd), len(sd), 1,
+                               (self.t.SensorDesc * len(sd))(*sd), len(sd), batch,
                                cfg["lambda_ref_m"], cfg["dt_s"], flags, ctypes.byref(h))
         assert rc == 0, self.lib.wfs_last_error()
         return h
@@ -114,6 +120,62 @@ def child_lds_of_every_device(L):
         assert L.lib.wfs_plan_destroy(h) == 0
 
 
+def _unjoined(lines, caller=0):
+    """Streams with work that the caller's stream does not wait for: `seen[s]` holds how many
+    launches of every stream the work of stream s comes after."""
+    count, seen, events = {}, {}, {}
+    for ln in lines:
+        kind, _, a, b = ln
+        if kind == "on":
+            count[a] = count.get(a, 0) + 1
+            seen.setdefault(a, {})[a] = count[a]
+        elif kind == "record":
+            events[b] = dict(seen.get(a, {}))
+        elif kind == "wait":
+            mine = seen.setdefault(a, {})
+            for k, v in events.get(b, {}).items():
+                mine[k] = max(mine.get(k, 0), v)
+    return [s for s, n in count.items() if seen.get(caller, {}).get(s, 0) < n]
+
+
+def child_second_streams(L):
+    """Whatever launch fails, the work that got as far as a second stream is waited for by the
+    caller's stream, whose owner may free the buffers after an error."""
+    fake = ctypes.c_void_p(4096)
+    cfg = _case(4, 2, 4)
+    cfg["sensors"].append(synth.configs._ngs(theta_x=0.0, theta_y=0.0, n_sa=1, n_sub=40,
+                                             n_fft=128, bin_=4, lam=1.65e-6, photons=0.0,
+                                             read_noise=0.0, pupil_d=6.0, obs_d=1.0))
+    cfg["layers"].append(dict(nx=8, ny=8, pitch_m=1.0, alt_m=0.0, vx_mps=0.0, vy_mps=0.0,
+                              weight=-1.0, boundary=1))
+    o = cfg["layers"][-1]["offset"] = cfg["layer_stride"]
+    cfg["layer_stride"] += 64
+    h = L.plan(cfg, batch=4)
+    n = ctypes.c_int64()
+    assert L.lib.wfs_calibrate_work(h, ctypes.byref(n)) == 0
+    work = (ctypes.c_float * n.value)()
+    calls = {"forward": lambda: L.lib.wfs_forward(h, fake, 0, 42, fake, None, None),
+             "calibrate": lambda: L.lib.wfs_calibrate(h, fake, o, 8, 0.1, 0, 42, fake, 1 << 20,
+                                                      None, work, n.value, None)}
+    for frames in range(4):
+        def steps(frames=frames):
+            assert L.lib.wfs_plan_set_schedule(h, -1, frames, -1, -1, -1, -1) == 0
+            return L.lib.wfs_forward_steps(h, fake, 0, 4, 42, fake, None, None)
+        calls["steps%d" % frames] = steps
+    for name, call in calls.items():
+        L.ops()
+        assert call() == 0, (name, L.lib.wfs_last_error())
+        ops = L.ops()
+        launches = sum(x[0] == "on" for x in ops)
+        assert launches > 2 and any(x[0] == "wait" for x in ops), (name, launches)
+        assert not _unjoined(ops), name
+        for i in range(launches):
+            L.rec.rec_fail_launch(i)
+            assert call() == L.t.WFS_EDEVICE, (name, i)
+            assert not _unjoined(L.ops()), (name, i, "of", launches)
+    L.rec.rec_fail_launch(-1)
+
+
 def _run(case, tmp_path):
     import pytest
     cxx = shutil.which("g++") or shutil.which("c++")
@@ -137,6 +199,10 @@ def test_adjoint_clears_its_images_outside_a_capture(tmp_path):
 
 def test_large_lds_is_allowed_on_every_device(tmp_path):
     _run("lds_of_every_device", tmp_path)
+
+
+def test_second_streams_are_joined_whatever_fails(tmp_path):
+    _run("second_streams", tmp_path)
 
 
 if __name__ == "__main__":
